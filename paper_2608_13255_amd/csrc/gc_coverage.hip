@@ -23,6 +23,7 @@
 // All counters are integers, so the reductions (wave ballots and shuffles,
 // block sums in LDS, one atomic per block and counter) are deterministic.
 #include "gc_common.h"
+#include "gc_compact.h"
 #include "gc_geometry.h"
 
 namespace gc {
@@ -59,32 +60,91 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
              max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
 }
 
-// grid: x = token chunks of kBlock, y = (u * B + b) * N + v.  A wave's
-// ballot gives two 32-token words of the row.
-__global__ __launch_bounds__(kBlock) void k_cov_pairs(const float* __restrict__ pos, const gc_camera* __restrict__ cams,
-                                                      const float* __restrict__ bbox, int B, int N, int H, int W,
-                                                      int wpr, uint32_t* __restrict__ bits) {
-  const int row = blockIdx.y;
-  const int v = row % N;
-  const int ub = row / N;
-  const int b = ub % B;
-  const int u = ub / B;
+constexpr int kPairBatch = 2;   // anchors whose tap loads a wave keeps in flight together (1: 45 us, 2 and 3: 35, 4: 39)
+
+// One block per chunk of kCompactTok tokens of a view (grid: x = chunk,
+// y = b * N + v), for every anchor u: the chunk's foreground tokens are
+// compacted once, the waves take the (anchors, group of 64 of them) items in
+// turn, each leaving one ballot per anchor, and the rows' bits are put
+// together from the ballots by the tokens' ranks.  The anchor is the same for
+// a whole wave, so its camera sits in scalar registers.
+// Bound by vector-ALU issue (25 of 35 us; two IEEE divisions and four tap
+// tests per pair).  8 assets x 12 views of 128 x 128: 78 -> 35 us against a
+// lane per raster token and anchor, which also formed the unused weights.
+__global__ __launch_bounds__(kCompactTok) void k_cov_pairs(const float* __restrict__ pos,
+                                                           const gc_camera* __restrict__ cams,
+                                                           const float* __restrict__ bbox, int B, int N, int H, int W,
+                                                           int wpr, uint32_t* __restrict__ bits) {
+  constexpr int kWords = kCompactTok / 32;         // words of bits per chunk and anchor
+  __shared__ CompactLds s;
+  __shared__ unsigned long long seen[GC_MAX_VIEWS][kCompactTok / 64];   // ballots: [anchor][group]
+  static_assert(sizeof(s.q) >= GC_MAX_VIEWS * kWords * 4, "the words take the positions' place");
+  uint32_t(*words)[kWords] = reinterpret_cast<uint32_t(*)[kWords]>(&s.q[0][0]);   // [anchor][word], after the last pair
+  const int bv = blockIdx.y;
+  const int b = bv / N, v = bv - b * N;
   const int HW = H * W;
-  const int p = blockIdx.x * kBlock + (int)threadIdx.x;
-  bool seen = false;
-  if (p < HW && u != v) {
-    const float* pp = pos + (((int64_t)b * N + v) * HW + p) * 3;
-    const float P[3] = {pp[0], pp[1], pp[2]};
-    if (finite_f(P[0]) && finite_f(P[1]) && finite_f(P[2])) {
-      const AnchorTaps at = anchor_taps(P, cams[(int64_t)b * N + u], pos + ((int64_t)b * N + u) * HW * 3, H, W, 4,
-                                        bbox[(int64_t)b * 8 + 6]);
-      seen = at.word != 0;
+  const int p0 = blockIdx.x * kCompactTok;
+  const int w0 = p0 / 32;
+  int n_fg;
+  const int rank = compact_foreground(pos + (int64_t)bv * HW * 3, HW, p0, s, &n_fg);
+  if (n_fg == 0) {   // a chunk of background: nothing to evaluate
+    for (int i = (int)threadIdx.x; i < N * kWords; i += kCompactTok) {
+      const int u = i / kWords, w = i - u * kWords;
+      if (w0 + w < wpr) bits[(((int64_t)u * B + b) * N + v) * wpr + w0 + w] = 0u;
     }
+    return;
   }
-  const unsigned long long m = __ballot(seen);
   const int lane = __lane_id();
-  const int w = p >> 5;
-  if ((lane & 31) == 0 && w < wpr) bits[(int64_t)row * wpr + w] = (uint32_t)(m >> (lane & 32));
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  const int groups = (n_fg + 63) / 64;
+  const float tol2 = bbox[(int64_t)b * 8 + 6];
+  const int batches = (N + kPairBatch - 1) / kPairBatch;
+  for (int it = wv; it < groups * batches; it += kCompactWaves) {
+    const int ub = it / groups, g = it - ub * groups;   // uniform
+    const int i = g * 64 + lane;
+    const bool live = i < n_fg;
+    const int j = live ? i : 0;
+    const float P[3] = {s.q[0][j], s.q[1][j], s.q[2][j]};
+    AnchorProj pj[kPairBatch];
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < kPairBatch; ++q) {   // a view past the last repeats the last one and is dropped
+      pj[q] = anchor_project(P, wave_camera(cams + (int64_t)b * N + min(ub * kPairBatch + q, N - 1)), H, W);
+      any |= pj[q].ok;
+    }
+    unsigned long long m[kPairBatch] = {};
+    if (__ballot(any & live)) {
+      TapPos tp[kPairBatch];
+#pragma unroll
+      for (int q = 0; q < kPairBatch; ++q)
+        tp[q] = anchor_tap_positions(pj[q], pos + ((int64_t)b * N + min(ub * kPairBatch + q, N - 1)) * HW * 3, H, W);
+#pragma unroll
+      for (int q = 0; q < kPairBatch; ++q) m[q] = __ballot(live & anchor_sees(P, pj[q], tp[q], H, W, tol2));
+    }
+#pragma unroll
+    for (int q = 0; q < kPairBatch; ++q)
+      if (lane == 0 && ub * kPairBatch + q < N) seen[ub * kPairBatch + q][g] = m[q];
+  }
+  __syncthreads();
+  // a token's bit for anchor u is bit rank % 32 of word rank / 32 of u's
+  // ballots; lane u of the wave collects the wave's two words for anchor u
+  const uint32_t mine = rank >= 0 ? 1u << (rank & 31) : 0u;
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(&seen[0][0]) + (rank >= 0 ? rank >> 5 : 0);
+  uint32_t lo = 0u, hi = 0u;
+  for (int u = 0; u < N; ++u) {
+    const unsigned long long m = __ballot((src[u * kWords] & mine) != 0u);
+    lo = lane == u ? (uint32_t)m : lo;
+    hi = lane == u ? (uint32_t)(m >> 32) : hi;
+  }
+  if (lane < N) {
+    words[lane][wv * 2] = lane == v ? 0u : lo;       // a view is no anchor of its own
+    words[lane][wv * 2 + 1] = lane == v ? 0u : hi;
+  }
+  __syncthreads();
+  for (int i = (int)threadIdx.x; i < N * kWords; i += kCompactTok) {
+    const int u = i / kWords, w = i - u * kWords;
+    if (w0 + w < wpr) bits[(((int64_t)u * B + b) * N + v) * wpr + w0 + w] = words[u][w];
+  }
 }
 
 __global__ void k_cov_init(const float* __restrict__ pos, int64_t n_tok, uint8_t* __restrict__ stale) {
@@ -746,8 +806,8 @@ extern "C" int gc_coverage_pairs(const float* pos, const gc_camera* cams, const 
   if (overlaps(pair_bits, nb, pos, (size_t)B * N * HW * 12) || overlaps(pair_bits, nb, cams, (size_t)B * N * sizeof(gc_camera)) ||
       overlaps(pair_bits, nb, bbox, (size_t)B * 32))
     return fail(GC_ERR_ALIAS, "gc_coverage_pairs: pair_bits overlaps an input");
-  const dim3 grid((unsigned)((HW + kBlock - 1) / kBlock), (unsigned)(N * B * N));
-  hipLaunchKernelGGL(k_cov_pairs, grid, dim3(kBlock), 0, stream, pos, cams, bbox, B, N, H, W, wpr, pair_bits);
+  const dim3 grid((unsigned)((HW + kCompactTok - 1) / kCompactTok), (unsigned)(B * N));
+  hipLaunchKernelGGL(k_cov_pairs, grid, dim3(kCompactTok), 0, stream, pos, cams, bbox, B, N, H, W, wpr, pair_bits);
   return after_launch(stream, "gc_coverage_pairs");
 }
 

@@ -20,8 +20,8 @@ struct AnchorTaps {
 // The operator for one pair runs in three steps so that callers can keep
 // several anchors' tap loads in flight: anchor_project (arithmetic only),
 // anchor_tap_positions (the four loads, all issued together) and
-// anchor_select (the tests, the selection and the weights).  anchor_taps
-// composes them for one anchor.
+// anchor_select (the tests, the selection and the weights), or anchor_sees
+// where only the visibility is wanted.
 
 struct AnchorProj {
   bool ok;          // the projection lands within two pixels of the grid
@@ -30,42 +30,47 @@ struct AnchorProj {
 };
 
 // P: the target token's 3D point (finite); cam: the anchor's camera.
+// Without branches: the camera's words are then loaded together (behind a
+// branch each would be a load of its own with its own wait), and an
+// orthographic camera's unused quotient costs less than that.  A comparison
+// with NaN is false, so the bounds of px and py reject what is not finite.
 __device__ __forceinline__ AnchorProj anchor_project(const float (&P)[3], const gc_camera& cam, int H, int W) {
-  AnchorProj o;
-  o.ok = false;
-  o.x0 = 0;
-  o.y0 = 0;
-  o.ax = 0.0f;
-  o.ay = 0.0f;
   const float* R = cam.R;
   const float xc = ((R[0] * P[0] + R[1] * P[1]) + R[2] * P[2]) + cam.t[0];
   const float yc = ((R[3] * P[0] + R[4] * P[1]) + R[5] * P[2]) + cam.t[1];
   const float zc = ((R[6] * P[0] + R[7] * P[1]) + R[8] * P[2]) + cam.t[2];
-  float px = 0.f, py = 0.f;
-  bool ok = true;
-  if (cam.model == 0) {
-    ok = zc > 0.0f;
-    if (ok) {
-      px = cam.fx * (xc / zc) + cam.cx;
-      py = cam.fy * (yc / zc) + cam.cy;
-    }
-  } else if (cam.model == 1) {
-    px = cam.fx * xc + cam.cx;
-    py = cam.fy * yc + cam.cy;
-  } else {
-    ok = false;
-  }
-  ok = ok && finite_f(px) && finite_f(py) &&
-       !(px < -2.0f || px > (float)W + 2.0f || py < -2.0f || py > (float)H + 2.0f);
-  if (!ok) return o;
-  const float gx = px - 0.5f, gy = py - 0.5f;
+  const bool pinhole = cam.model == 0;
+  const float qx = xc / zc, qy = yc / zc;
+  const float px = cam.fx * (pinhole ? qx : xc) + cam.cx;
+  const float py = cam.fy * (pinhole ? qy : yc) + cam.cy;
+  AnchorProj o;
+  o.ok = (pinhole ? zc > 0.0f : cam.model == 1) & (px >= -2.0f) & (px <= (float)W + 2.0f) & (py >= -2.0f) &
+         (py <= (float)H + 2.0f);
+  const float gx = o.ok ? px - 0.5f : 0.0f, gy = o.ok ? py - 0.5f : 0.0f;
   const float fx0 = floorf(gx), fy0 = floorf(gy);
-  o.ok = true;
   o.ax = gx - fx0;
   o.ay = gy - fy0;
   o.x0 = (int)fx0;
   o.y0 = (int)fy0;
   return o;
+}
+
+// A camera the whole wave uses, in scalar registers: all its words are loaded
+// together here (left alone, the compiler sinks parts of the load behind the
+// camera model's branch, each with a wait of its own).  Through the constant
+// address space, since nothing writes cameras while a kernel runs.
+__device__ __forceinline__ gc_camera wave_camera(const gc_camera* cam) {
+  static_assert(sizeof(gc_camera) == 68, "17 words");
+  typedef const __attribute__((address_space(4))) uint32_t* ConstWords;
+  const ConstWords src = (ConstWords)(uintptr_t)cam;
+  uint32_t w[17];
+#pragma unroll
+  for (int i = 0; i < 17; ++i) w[i] = src[i];
+#pragma unroll
+  for (int i = 0; i < 17; ++i) asm volatile("" : "+s"(w[i]));
+  gc_camera c;
+  __builtin_memcpy(&c, w, sizeof(c));
+  return c;
 }
 
 // Positions of the four taps (x0 + (k & 1), y0 + (k >> 1)) of the anchor
@@ -77,20 +82,55 @@ struct TapPos {
 };
 
 __device__ __forceinline__ TapPos anchor_tap_positions(const AnchorProj& pj, const float* src, int H, int W) {
-  // a view has fewer than 2^24 pixels, so the offsets within it are 32-bit
-  const uint32_t xa = (uint32_t)min(max(pj.x0, 0), W - 1), xb = (uint32_t)min(max(pj.x0 + 1, 0), W - 1);
-  const uint32_t ra = (uint32_t)min(max(pj.y0, 0), H - 1) * (uint32_t)W;
-  const uint32_t rb = (uint32_t)min(max(pj.y0 + 1, 0), H - 1) * (uint32_t)W;
-  const uint32_t px[4] = {ra + xa, ra + xb, rb + xa, rb + xb};
+  // grids have at most 4094 rows and columns: a row's byte offset is a product
+  // of 24-bit factors, and every byte offset within the view is 32-bit
+  const uint32_t row = 12u * (uint32_t)W;
+  const uint32_t xa = 12u * (uint32_t)min(max(pj.x0, 0), W - 1), xb = 12u * (uint32_t)min(max(pj.x0 + 1, 0), W - 1);
+  const uint32_t ra = __umul24((uint32_t)min(max(pj.y0, 0), H - 1), row);
+  const uint32_t rb = __umul24((uint32_t)min(max(pj.y0 + 1, 0), H - 1), row);
+  const uint32_t at[4] = {ra + xa, ra + xb, rb + xa, rb + xb};
   TapPos t;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const float* Q = src + px[k] * 3u;
+    const float* Q = reinterpret_cast<const float*>(reinterpret_cast<const char*>(src) + at[k]);
     t.q[k][0] = Q[0];
     t.q[k][1] = Q[1];
     t.q[k][2] = Q[2];
   }
   return t;
+}
+
+// The per-tap tolerance test: valid[k] when tap k lies on the grid, is
+// finite and at most sqrt(tol2) away from P; d2[k]: its squared distance
+// (any value where it is not valid).  A NaN in the tap makes the distance NaN
+// and an infinite one makes it infinite, so the comparison with a finite
+// tolerance decides the tap's finiteness too: its components are looked at
+// only when the tolerance itself overflowed to infinity.  pj.ok must hold.
+__device__ __forceinline__ void taps_in_tolerance(const float (&P)[3], const AnchorProj& pj, const TapPos& tp, int H,
+                                                  int W, float tol2, bool (&valid)[4], float (&d2)[4]) {
+  const bool in_x[2] = {(uint32_t)pj.x0 < (uint32_t)W, (uint32_t)(pj.x0 + 1) < (uint32_t)W};
+  const bool in_y[2] = {(uint32_t)pj.y0 < (uint32_t)H, (uint32_t)(pj.y0 + 1) < (uint32_t)H};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float dx = tp.q[k][0] - P[0], dy = tp.q[k][1] - P[1], dz = tp.q[k][2] - P[2];
+    d2[k] = (dx * dx + dy * dy) + dz * dz;
+    valid[k] = in_x[k & 1] & in_y[k >> 1] & (d2[k] <= tol2);
+  }
+  if (__ballot(!finite_f(tol2))) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      valid[k] = valid[k] && finite_f(tp.q[k][0]) && finite_f(tp.q[k][1]) && finite_f(tp.q[k][2]);
+  }
+}
+
+// Whether the anchor sees P: some tap is valid (the word of anchor_select is
+// non-zero exactly then).
+__device__ __forceinline__ bool anchor_sees(const float (&P)[3], const AnchorProj& pj, const TapPos& tp, int H, int W,
+                                            float tol2) {
+  bool valid[4];
+  float d2[4];
+  taps_in_tolerance(P, pj, tp, H, W, tol2, valid, d2);
+  return pj.ok & (valid[0] | valid[1] | valid[2] | valid[3]);
 }
 
 // The per-tap tolerance test, the K nearest valid taps and their normalised
@@ -107,22 +147,10 @@ __device__ __forceinline__ AnchorTaps anchor_select(const float (&P)[3], const A
   const float ax = pj.ax, ay = pj.ay;
   bool valid[4];
   float d2[4];
+  taps_in_tolerance(P, pj, tp, H, W, tol2, valid, d2);
   int nvalid = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int x = x0 + (k & 1), y = y0 + (k >> 1);
-    valid[k] = false;
-    d2[k] = 0.0f;
-    if (x < 0 || x >= W || y < 0 || y >= H) continue;
-    const float qx = tp.q[k][0], qy = tp.q[k][1], qz = tp.q[k][2];
-    if (!(finite_f(qx) && finite_f(qy) && finite_f(qz))) continue;
-    const float dx = qx - P[0], dy = qy - P[1], dz = qz - P[2];
-    const float dd = (dx * dx + dy * dy) + dz * dz;
-    if (!(dd <= tol2)) continue;
-    valid[k] = true;
-    d2[k] = dd;
-    ++nvalid;
-  }
+  for (int k = 0; k < 4; ++k) nvalid += valid[k] ? 1 : 0;
   if (nvalid == 0) return o;
   bool sel[4] = {false, false, false, false};
   if (nvalid <= K) {
@@ -167,15 +195,6 @@ __device__ __forceinline__ AnchorTaps anchor_select(const float (&P)[3], const A
   }
   o.word = (int32_t)((uint32_t)(x0 + 1) | ((uint32_t)(y0 + 1) << 12) | ((uint32_t)o.mask << 24));
   return o;
-}
-
-// P: the target token's 3D point (finite); cam: the anchor's camera;
-// src: the anchor view's position map [H][W][3]; tol2: squared tolerance.
-__device__ __forceinline__ AnchorTaps anchor_taps(const float (&P)[3], const gc_camera& cam, const float* src, int H,
-                                                  int W, int K, float tol2) {
-  const AnchorProj pj = anchor_project(P, cam, H, W);
-  const TapPos tp = anchor_tap_positions(pj, src, H, W);
-  return anchor_select(P, pj, tp, H, W, K, tol2);
 }
 
 }  // namespace gc

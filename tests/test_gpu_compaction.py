@@ -1,0 +1,83 @@
+"""The kernels that evaluate the operator on compacted foreground tokens (the
+correspondence builder, with and without counters, and the visibility pairs),
+at the sizes where a chunk of 256 tokens or a group of 64 begins or ends:
+words, pair bits and counters bit-exact against the oracle, weights within a
+few float roundings of a quotient (1e-6).  Maps full of foreground, without
+any, with one token and with random holes; NaN and infinite positions as
+background; pinhole and orthographic cameras in one rig; anchor counts on both
+sides of the four- and eight-lane groups; a squared tolerance that overflowed
+to infinity, which every finite tap on the grid satisfies."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+from conftest import visible_weights
+from test_gpu_limits import sphere_problem
+from test_gpu_properties import random_rig
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def gc():
+    import paper_2608_13255_amd as gc
+    return gc
+
+
+def problem(seed, N, H, W, fill):
+    rs, P, cams = sphere_problem(seed, N, H, W)
+    pin = random_rig(rs, N, H, W, True)
+    for k in cams:                       # every other camera is a pinhole
+        cams[k][0, 1::2] = pin[k][1::2]
+    P = P.copy()
+    if fill == "all":
+        P = np.where(np.isfinite(P), P, rs.uniform(-0.5, 0.5, P.shape).astype(np.float32))
+    elif fill == "none":
+        P[:] = np.nan
+    elif fill == "one":
+        keep = P[0, :, H // 2, W // 2].copy()
+        P[:] = np.nan
+        P[0, :, H // 2, W // 2] = np.where(np.isfinite(keep), keep, 0.1)
+    else:
+        hole = rs.random(P.shape[:-1]) < 0.3
+        P[hole] = np.where(rs.random((int(hole.sum()), 1)) < 0.5, np.float32(np.nan), np.float32(np.inf))
+    return rs, P, cams
+
+
+@pytest.mark.parametrize("N,H,W,a,K,fill", [
+    (3, 1, 1, 1, 4, "all"), (3, 1, 63, 2, 4, "all"), (4, 8, 8, 3, 1, "holes"), (4, 5, 13, 4, 4, "all"),
+    (5, 15, 17, 4, 4, "holes"), (5, 16, 16, 4, 2, "all"), (6, 257, 1, 5, 4, "all"), (6, 16, 20, 5, 3, "holes"),
+    (9, 23, 31, 8, 4, "holes"), (4, 32, 33, 2, 4, "none"), (4, 32, 33, 2, 4, "one"), (9, 33, 32, 1, 4, "all")])
+@pytest.mark.parametrize("overflow", [False, True])
+def test_builder_and_pairs_match_oracle(gc, N, H, W, a, K, fill, overflow):
+    rs, P, cams = problem(7 + N * H + W, N, H, W, fill)
+    bb = oracle.bbox(P, 0.05).reshape(1, -1).copy()
+    if overflow:
+        bb[:, 6] = np.inf
+    anchors = sorted(rs.choice(N, a, replace=False).tolist())
+    corr_o, wts_o, nvis_o = oracle.build(P, cams, anchors, K, bb)
+    Pd, cams_d = torch.from_numpy(P).to(DEV), gc.camera_tensor(cams, DEV)
+    full = np.zeros((1, 8), np.float32)
+    full[:, :bb.shape[1]] = bb
+    bbd = torch.from_numpy(full).to(DEV)
+    for counted in (False, True):
+        stats = torch.full((1, 4), 77, dtype=torch.int32, device=DEV) if counted else None
+        corr = torch.full((1, N - a, H, W, a), -1, dtype=torch.int32, device=DEV)
+        wts = torch.zeros((1, N - a, H, W, a, K), dtype=torch.float32, device=DEV)
+        gc.gc_build_correspondence(Pd, cams_d, anchors, K, bbd, corr=corr, weights=wts, stats=stats)
+        np.testing.assert_array_equal(corr.cpu().numpy(), corr_o)
+        assert np.abs(visible_weights(corr, wts) - wts_o).max(initial=0.0) <= 1e-6
+        if counted:
+            targets = [v for v in range(N) if v not in anchors]
+            want = [int((corr_o != 0).sum()), int((nvis_o > 0).sum()),
+                    int(np.isfinite(P[:, targets]).all(-1).sum()),
+                    int(sum(((corr_o >> (24 + k)) & 1).sum() for k in range(4)))]
+            assert stats.cpu().numpy()[0].tolist() == want
+    pb = gc.gc_coverage_pairs(Pd, cams_d, bbd).cpu().numpy().view(np.uint32)
+    un = np.unpackbits(np.ascontiguousarray(pb).view(np.uint8), axis=-1, bitorder="little")
+    un = un.reshape(N, 1, N, -1)
+    assert not un[..., H * W:].any()
+    np.testing.assert_array_equal(un[..., :H * W].reshape(N, 1, N, H, W), oracle.coverage_pairs(P, cams, 4, bb))
