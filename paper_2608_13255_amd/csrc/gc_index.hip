@@ -20,13 +20,22 @@
 // entries, so its tokens form a compact patch of the view, whose footprints
 // in each anchor view lie close together: their tap reads share cache lines.
 //
-// Three passes, deterministic:
-//   count    per 1024-entry chunk of the list order, listed tokens (ballot +
-//            popcount); also writes the bitmask in token order (one 64-bit
-//            ballot per wave over consecutive tokens)
-//   scan     exclusive prefix over the chunk counts, total -> list length
-//   scatter  each chunk writes its tokens at its offset, ranked inside the
-//            chunk by (round, wave, mbcnt of the ballot)
+// Two passes, deterministic:
+//   bits     streams the input once in token order: one 64-bit ballot per wave
+//            gives the bitmask, and each chunk of 1024 tokens its count
+//   scatter  a block per 1024 consecutive list positions, from the bitmask
+//            alone (32 or 96 times smaller than the input): token order and
+//            list order agree at the start of every band, so the number of
+//            listed tokens in front of the block is the sum of the counts up
+//            to its band, plus the bits of its band's columns and tile rows in
+//            front of it; inside the block tokens are ranked by (round, wave,
+//            mbcnt of the ballot)
+// Above kPrefixChunks chunks a one-block pass between the two turns the counts
+// into offsets.
+// Bound by launches and latency up to the stress size: 8 assets x 8 target
+// views of 128 x 128 with 4 anchors 19.9 -> 9.0 us, the 12 views' foreground
+// 29.3 -> 14.4 us against count, scan and scatter passes that each read the
+// input (one pass twice); one 64 x 64 asset 12.2 -> 6.3 us.
 #include <mutex>
 
 #include "gc_common.h"
@@ -45,22 +54,41 @@ constexpr int kChunk = kRounds * kBlock;
 constexpr int kWaves = kBlock / 64;
 constexpr int kTile = 16;                  // tiles of the list order: kTile x kTile tokens
 
+// Up to here every scatter block sums the counts in front of it itself; the
+// foreground index of 6144 / 16,200 / 49,152 chunks took 43 / 111 / 571 us so
+// and 65 / 156 / 504 us with the scan pass in between.
+constexpr int64_t kPrefixChunks = 16384;
+
 // Position i of the list order -> token index; a bijection of
 // [0, n_views * H * W) (no padding: edge tiles are narrower or shorter).
 struct TileOrder {
-  int H, W;
-  int64_t HW;
-  __device__ __forceinline__ int64_t token(int64_t i) const {
-    const int64_t view = i / HW;
-    const int r = (int)(i - view * HW);           // position inside the view
-    const int band = r / (kTile * W);             // band of kTile rows (the last may be shorter)
-    const int rb = r - band * kTile * W;
-    const int bh = min(kTile, H - band * kTile);  // rows of this band
-    const int tx = rb / (bh * kTile);             // tile inside the band (the last may be narrower)
-    const int q = rb - tx * bh * kTile;
-    const int tw = min(kTile, W - tx * kTile);    // columns of this tile
-    const int yy = q / tw;
-    return view * HW + (int64_t)(band * kTile + yy) * W + tx * kTile + (q - yy * tw);
+  uint32_t H, W, HW;
+  struct Place {
+    uint32_t band0;   // token (and list position) of the first token of i's band
+    uint32_t bh;      // rows of the band (the last of a view may be shorter)
+    uint32_t col0;    // first column of i's tile
+    uint32_t tw;      // columns of the tile (the last of a band may be narrower)
+    uint32_t yy, xx;  // i's row and column inside the tile
+  };
+  __device__ __forceinline__ Place place(uint32_t i) const {
+    Place o;
+    const uint32_t view = i / HW;
+    const uint32_t r = i - view * HW;              // position inside the view
+    const uint32_t band = r / (kTile * W);
+    const uint32_t rb = r - band * kTile * W;
+    o.band0 = i - rb;
+    o.bh = min((uint32_t)kTile, H - band * kTile);
+    const uint32_t tx = rb / (o.bh * kTile);       // tile inside the band
+    const uint32_t q = rb - tx * o.bh * kTile;
+    o.col0 = tx * kTile;
+    o.tw = min((uint32_t)kTile, W - o.col0);
+    o.yy = q / o.tw;
+    o.xx = q - o.yy * o.tw;
+    return o;
+  }
+  __device__ __forceinline__ uint32_t token(uint32_t i) const {
+    const Place o = place(i);
+    return o.band0 + o.yy * W + o.col0 + o.xx;
   }
 };
 
@@ -97,31 +125,36 @@ struct ForegroundPred {
   }
 };
 
+// The bitmask in token order, and the listed tokens of each chunk.
 template <class Pred>
-__global__ __launch_bounds__(kBlock) void k_index_count(Pred pred, TileOrder order, int64_t n_tokens,
-                                                        uint32_t* __restrict__ bits, int64_t n_words,
-                                                        int32_t* __restrict__ counts) {
+__global__ __launch_bounds__(kBlock) void k_index_bits(Pred pred, int64_t n_tokens, uint32_t* __restrict__ bits,
+                                                       int64_t n_words, int32_t* __restrict__ counts) {
   __shared__ int32_t wave_cnt[kWaves];
   const int wv = threadIdx.x / 64;
-  int32_t total = 0;
+  bool on[kRounds];
+#pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     const int64_t i = (int64_t)blockIdx.x * kChunk + r * kBlock + threadIdx.x;
-    // the bitmask over consecutive tokens
-    const unsigned long long m = __ballot(i < n_tokens && pred(i));
+    on[r] = pred(i < n_tokens ? i : n_tokens - 1) && i < n_tokens;
+  }
+  int32_t mine = 0;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const unsigned long long m = __ballot(on[r]);
+    mine += __popcll(m);
     if (__lane_id() == 0) {
       const int64_t w0 = ((int64_t)blockIdx.x * kChunk + r * kBlock + wv * 64) >> 5;
       if (w0 < n_words) bits[w0] = (uint32_t)m;
       if (w0 + 1 < n_words) bits[w0 + 1] = (uint32_t)(m >> 32);
     }
-    // the count over this chunk of the list order
-    const unsigned long long c = __ballot(i < n_tokens && pred(order.token(i)));
-    if (__lane_id() == 0) wave_cnt[wv] = __popcll(c);
-    __syncthreads();
-    if (threadIdx.x == 0)
-      for (int w = 0; w < kWaves; ++w) total += wave_cnt[w];
-    __syncthreads();
   }
-  if (threadIdx.x == 0) counts[blockIdx.x] = total;
+  if (__lane_id() == 0) wave_cnt[wv] = mine;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t total = 0;
+    for (int w = 0; w < kWaves; ++w) total += wave_cnt[w];
+    counts[blockIdx.x] = total;
+  }
 }
 
 // one block: exclusive scan of counts[n] into offsets[n], total into n_vis
@@ -149,30 +182,82 @@ __global__ __launch_bounds__(kBlock) void k_index_scan(const int32_t* __restrict
   if (threadIdx.x == 0) *n_vis = carry;
 }
 
-template <class Pred>
-__global__ __launch_bounds__(kBlock) void k_index_scatter(Pred pred, TileOrder order, int64_t n_tokens,
-                                                          const int32_t* __restrict__ offsets,
-                                                          int32_t* __restrict__ list) {
-  __shared__ int32_t wave_cnt[kWaves];
-  const int wv = threadIdx.x / 64;
-  int32_t pos = offsets[blockIdx.x];
-  for (int r = 0; r < kRounds; ++r) {
-    const int64_t i = (int64_t)blockIdx.x * kChunk + r * kBlock + threadIdx.x;
-    const int64_t tok = i < n_tokens ? order.token(i) : 0;
-    const bool vis = i < n_tokens && pred(tok);
-    const unsigned long long m = __ballot(vis);
-    if (__lane_id() == 0) wave_cnt[wv] = __popcll(m);
-    __syncthreads();
-    int32_t before = 0;
-    for (int w = 0; w < wv; ++w) before += wave_cnt[w];
-    const int32_t rank = (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    if (vis) pred.write(list, pos + before + rank, tok);
-    int32_t round_total = 0;
-    for (int w = 0; w < kWaves; ++w) round_total += wave_cnt[w];
-    __syncthreads();
-    pos += round_total;
+// Set bits among tokens [first, first + n) that fall to lane `lane` of `lanes`
+// lanes sharing the range word by word.
+__device__ __forceinline__ int32_t count_bits(const uint32_t* __restrict__ bits, uint32_t first, uint32_t n, int lane,
+                                              int lanes) {
+  int32_t c = 0;
+  if (n == 0) return c;
+  const uint32_t last = first + n - 1;
+  for (uint32_t w = (first >> 5) + lane; w <= last >> 5; w += lanes) {
+    uint32_t x = bits[w];
+    if (w == first >> 5) x &= ~0u << (first & 31);
+    if (w == last >> 5) x &= ~0u >> (31 - (last & 31));
+    c += __popc(x);
   }
+  return c;
+}
+
+// prefix: counts per token chunk (SCANNED: their exclusive offsets).
+template <class Pred, bool SCANNED>
+__global__ __launch_bounds__(kBlock) void k_index_scatter(Pred pred, TileOrder order, int64_t n_tokens,
+                                                          const uint32_t* __restrict__ bits,
+                                                          const int32_t* __restrict__ prefix,
+                                                          int32_t* __restrict__ list, int32_t* __restrict__ n_listed) {
+  __shared__ int32_t wave_cnt[kRounds][kWaves];
+  __shared__ int32_t wave_before[kWaves];
+  const int wv = threadIdx.x / 64;
+  const int64_t q0 = (int64_t)blockIdx.x * kChunk;
+  uint32_t tok[kRounds], word[kRounds];
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int64_t i = q0 + r * kBlock + threadIdx.x;
+    tok[r] = order.token((uint32_t)(i < n_tokens ? i : n_tokens - 1));
+    word[r] = bits[tok[r] >> 5];
+  }
+  // listed tokens in front of this block: tokens before its band, then, row
+  // by row of the band (16 lanes each), the columns in front of it
+  const TileOrder::Place at = order.place((uint32_t)q0);
+  const uint32_t chunk0 = at.band0 / kChunk;
+  int32_t before = 0;
+  if (SCANNED) {
+    if (threadIdx.x == 0) before = prefix[chunk0];
+  } else {
+    for (uint32_t c = threadIdx.x; c < chunk0; c += kBlock) before += prefix[c];
+  }
+  if (threadIdx.x < 32) before += count_bits(bits, chunk0 * kChunk, at.band0 - chunk0 * kChunk, threadIdx.x, 32);
+  const uint32_t row = threadIdx.x / 16;
+  if (row < at.bh) {
+    const uint32_t cols = at.col0 + (row < at.yy ? at.tw : row == at.yy ? at.xx : 0u);
+    before += count_bits(bits, at.band0 + row * order.W, cols, threadIdx.x % 16, 16);
+  }
+  for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
+  unsigned long long m[kRounds];
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r)
+    m[r] = __ballot(q0 + r * kBlock + threadIdx.x < n_tokens && ((word[r] >> (tok[r] & 31)) & 1u));
+  if (__lane_id() == 0) {
+    wave_before[wv] = before;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) wave_cnt[r][wv] = __popcll(m[r]);
+  }
+  __syncthreads();
+  int32_t pos = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) pos += wave_before[w];
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    int32_t mine = pos;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      mine += w < wv ? wave_cnt[r][w] : 0;
+      pos += wave_cnt[r][w];
+    }
+    const int32_t rank = (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m[r] >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)m[r], 0u));
+    if ((m[r] >> __lane_id()) & 1ull) pred.write(list, mine + rank, tok[r]);
+  }
+  if (threadIdx.x == 0 && q0 + kChunk >= n_tokens) *n_listed = pos;   // the last block's end is the list's length
 }
 
 }  // namespace
@@ -197,9 +282,9 @@ int check_views(int64_t n_views, int H, int W, const char* who, int64_t* n_token
   if (n_views > 0x7fffffffLL / ((int64_t)H * W))
     return fail(GC_ERR_CAPACITY, "%s: n_views * H * W exceeds 2^31-1", who);
   *n_tokens = n_views * H * W;
-  order->H = H;
-  order->W = W;
-  order->HW = (int64_t)H * W;
+  order->H = (uint32_t)H;
+  order->W = (uint32_t)W;
+  order->HW = (uint32_t)H * (uint32_t)W;
   return GC_OK;
 }
 
@@ -220,21 +305,26 @@ int check_visible_index(const int32_t* corr, int64_t n_tokens, int a, const uint
   return GC_OK;
 }
 
-// The three passes; counts_offsets: 2 * ceil(n_tokens / kChunk) int32 of
-// device scratch, fully written before it is read.
-void launch_visible_index(const int32_t* corr, int64_t n_tokens, const TileOrder& order, int a, uint32_t* vis_bits,
-                          int32_t* vis_list, int32_t* n_vis, int32_t* counts_offsets, hipStream_t stream) {
+// The passes; counts_offsets: 2 * ceil(n_tokens / kChunk) int32 of device
+// scratch, fully written before it is read.
+template <class Pred>
+void launch_index(const Pred& pred, int64_t n_tokens, const TileOrder& order, uint32_t* bits, int32_t* list,
+                  int32_t* n_listed, int32_t* counts_offsets, hipStream_t stream) {
   const int64_t n_words = (n_tokens + 31) / 32;
   const int64_t nb = n_tokens > 0 ? (n_tokens + kChunk - 1) / kChunk : 0;
   int32_t* counts = counts_offsets;
   int32_t* offsets = counts + nb;
   if (nb > 0)
-    hipLaunchKernelGGL(k_index_count<VisiblePred>, dim3((unsigned)nb), dim3(kBlock), 0, stream,
-                       VisiblePred{corr, a}, order, n_tokens, vis_bits, n_words, counts);
-  hipLaunchKernelGGL(k_index_scan, dim3(1), dim3(kBlock), 0, stream, counts, nb, offsets, n_vis);
-  if (nb > 0)
-    hipLaunchKernelGGL(k_index_scatter<VisiblePred>, dim3((unsigned)nb), dim3(kBlock), 0, stream,
-                       VisiblePred{corr, a}, order, n_tokens, offsets, vis_list);
+    hipLaunchKernelGGL(k_index_bits<Pred>, dim3((unsigned)nb), dim3(kBlock), 0, stream, pred, n_tokens, bits, n_words,
+                       counts);
+  if (nb == 0 || nb > kPrefixChunks)
+    hipLaunchKernelGGL(k_index_scan, dim3(1), dim3(kBlock), 0, stream, counts, nb, offsets, n_listed);
+  if (nb > kPrefixChunks)
+    hipLaunchKernelGGL((k_index_scatter<Pred, true>), dim3((unsigned)nb), dim3(kBlock), 0, stream, pred, order,
+                       n_tokens, bits, offsets, list, n_listed);
+  else if (nb > 0)
+    hipLaunchKernelGGL((k_index_scatter<Pred, false>), dim3((unsigned)nb), dim3(kBlock), 0, stream, pred, order,
+                       n_tokens, bits, counts, list, n_listed);
 }
 
 // Device address of this library's scratch array on the current device,
@@ -283,7 +373,7 @@ extern "C" int gc_index_correspondence(const int32_t* corr, int64_t n_views, int
   if (overlaps(workspace, workspace_bytes, corr, nc) || overlaps(workspace, workspace_bytes, vis_list, nl) ||
       overlaps(workspace, workspace_bytes, vis_bits, nbits) || overlaps(workspace, workspace_bytes, n_vis, 4))
     return fail(GC_ERR_ALIAS, "%s: buffers overlap", who);
-  launch_visible_index(corr, n_tokens, order, a, vis_bits, vis_list, n_vis, static_cast<int32_t*>(workspace), stream);
+  launch_index(VisiblePred{corr, a}, n_tokens, order, vis_bits, vis_list, n_vis, static_cast<int32_t*>(workspace), stream);
   return after_launch(stream, who);
 }
 
@@ -304,7 +394,7 @@ extern "C" int gc_index_correspondence_noalloc(const int32_t* corr, int64_t n_vi
   void* ws = nullptr;
   rc = scratch_on_current_device(&ws, who);
   if (rc) return rc;
-  launch_visible_index(corr, n_tokens, order, a, vis_bits, vis_list, n_vis, static_cast<int32_t*>(ws), stream);
+  launch_index(VisiblePred{corr, a}, n_tokens, order, vis_bits, vis_list, n_vis, static_cast<int32_t*>(ws), stream);
   return after_launch(stream, who);
 }
 
@@ -331,15 +421,6 @@ extern "C" int gc_index_foreground(const float* pos, int64_t n_views, int H, int
       overlaps(workspace, workspace_bytes, pos, np) || overlaps(workspace, workspace_bytes, fg_recs, nr) ||
       overlaps(workspace, workspace_bytes, fg_bits, nbits) || overlaps(workspace, workspace_bytes, n_fg, 4))
     return fail(GC_ERR_ALIAS, "foreground index: buffers overlap");
-  const int64_t nb = n_tokens > 0 ? (n_tokens + kChunk - 1) / kChunk : 0;
-  int32_t* counts = static_cast<int32_t*>(workspace);
-  int32_t* offsets = counts + nb;
-  if (nb > 0)
-    hipLaunchKernelGGL(k_index_count<ForegroundPred>, dim3((unsigned)nb), dim3(kBlock), 0, stream,
-                       ForegroundPred{pos}, order, n_tokens, fg_bits, n_words, counts);
-  hipLaunchKernelGGL(k_index_scan, dim3(1), dim3(kBlock), 0, stream, counts, nb, offsets, n_fg);
-  if (nb > 0)
-    hipLaunchKernelGGL(k_index_scatter<ForegroundPred>, dim3((unsigned)nb), dim3(kBlock), 0, stream,
-                       ForegroundPred{pos}, order, n_tokens, offsets, fg_recs);
+  launch_index(ForegroundPred{pos}, n_tokens, order, fg_bits, fg_recs, n_fg, static_cast<int32_t*>(workspace), stream);
   return after_launch(stream, "gc_index_foreground");
 }
