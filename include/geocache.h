@@ -528,7 +528,7 @@ int gc_transport_unipc_geom(const void* x0_prev, const void* x0_anchor_new, cons
  *   mask (the token's own view and the views that see it) -- whose last block
  *   takes its subset sums Y and runs every round, the gain of u given the
  *   chosen set S being Y[all \ S] - Y[all \ (S + u)]; with more views,
- *   2 (a - n_forced) launches.  One launch when every view is forced.  Never
+ *   a - n_forced + 1 launches.  One launch when every view is forced.  Never
  *   synchronises.
  * gc_coverage_score: scores (device uint64 [M], overwritten) = the weighted
  *   coverage, sum of 1 + staleness over the foreground tokens it covers, of
@@ -542,8 +542,9 @@ int gc_transport_unipc_geom(const void* x0_prev, const void* x0_anchor_new, cons
  *   anchors_out, workspace) on the updated staleness -- the end of one step
  *   and the choice for the next in one pass over the tokens when N <= 12
  *   (two launches; the statistics are summed with integer atomics, so the
- *   result is the same as the two calls').  With more views, the two calls'
- *   launches.  stats must not overlap the workspace or anchors_out.
+ *   result is the same as the two calls').  With more views, the selection's
+ *   launches, the step applied by the first and the statistics taken by the
+ *   last.  stats must not overlap the workspace or anchors_out.
  * gc_coverage_update_score: gc_coverage_update, then gc_coverage_score of
  *   the M sets of a_set views on the updated staleness, fused as above.
  * gc_schedule_refresh_due: host; stats as written by gc_coverage_update and

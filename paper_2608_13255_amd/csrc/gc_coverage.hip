@@ -181,44 +181,65 @@ __device__ __forceinline__ uint32_t valid_bits(int HW, int wi) {
   return n >= 32 ? ~0u : (n <= 0 ? 0u : (1u << n) - 1u);
 }
 
-// Staleness bytes of tokens t0 .. t0 + 31 of a row, four per register (token
-// t0 + 4k + j in byte j of d[k]); tokens past the row read as background.
-// VEC: the row starts 16-byte aligned and holds a multiple of 16 tokens.
-template <bool VEC>
-__device__ __forceinline__ void load_word_bytes(const uint8_t* __restrict__ row, int HW, int t0, uint32_t (&d)[8]) {
-  if constexpr (VEC) {
-    const uint4 bg = make_uint4(~0u, ~0u, ~0u, ~0u);
-    const uint4 lo = t0 < HW ? *reinterpret_cast<const uint4*>(row + t0) : bg;
-    const uint4 hi = t0 + 16 < HW ? *reinterpret_cast<const uint4*>(row + t0 + 16) : bg;
-    d[0] = lo.x; d[1] = lo.y; d[2] = lo.z; d[3] = lo.w;
-    d[4] = hi.x; d[5] = hi.y; d[6] = hi.z; d[7] = hi.w;
-  } else {
+// Unaligned vectors: the hardware reads and writes them at any byte, so a
+// row's bytes move in wide accesses whatever H * W and the buffer's address.
+typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32_u __attribute__((aligned(1)));
+
+// Staleness bytes of tokens t0 .. t0 + 4 n - 1 of a row, four per register
+// (token t0 + 4k + j in byte j of d[k]); tokens past the row read as
+// background.  n = 8 (a pair word's tokens) or 2.
+template <int n>
+__device__ __forceinline__ void load_bytes(const uint8_t* __restrict__ row, int HW, int t0, uint32_t (&d)[n]) {
+  if (t0 + 4 * n <= HW) {
+    if constexpr (n == 8) {
+      const u32x4_u lo = *reinterpret_cast<const u32x4_u*>(row + t0);
+      const u32x4_u hi = *reinterpret_cast<const u32x4_u*>(row + t0 + 16);
+      d[0] = lo.x; d[1] = lo.y; d[2] = lo.z; d[3] = lo.w;
+      d[4] = hi.x; d[5] = hi.y; d[6] = hi.z; d[7] = hi.w;
+    } else {
+      const u32x2_u q = *reinterpret_cast<const u32x2_u*>(row + t0);
+      d[0] = q.x;
+      d[1] = q.y;
+    }
+  } else {   // the row's end
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      uint32_t x = 0u;
+    for (int k = 0; k < n; ++k) {
+      const int t = t0 + 4 * k;
+      if (t + 4 <= HW) {
+        d[k] = *reinterpret_cast<const u32_u*>(row + t);
+      } else {
+        uint32_t x = 0u;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int t = t0 + 4 * k + j;
-        x |= (t < HW ? (uint32_t)row[t] : 0xffu) << (8 * j);
+        for (int j = 0; j < 4; ++j) x |= (t + j < HW ? (uint32_t)row[t + j] : 0xffu) << (8 * j);
+        d[k] = x;
       }
-      d[k] = x;
     }
   }
 }
 
-template <bool VEC>
-__device__ __forceinline__ void store_word_bytes(uint8_t* __restrict__ row, int HW, int t0, const uint32_t (&d)[8]) {
-  if constexpr (VEC) {
-    if (t0 < HW) *reinterpret_cast<uint4*>(row + t0) = make_uint4(d[0], d[1], d[2], d[3]);
-    if (t0 + 16 < HW) *reinterpret_cast<uint4*>(row + t0 + 16) = make_uint4(d[4], d[5], d[6], d[7]);
+template <int n>
+__device__ __forceinline__ void store_bytes(uint8_t* __restrict__ row, int HW, int t0, const uint32_t (&d)[n]) {
+  if (t0 + 4 * n <= HW) {
+    if constexpr (n == 8) {
+      *reinterpret_cast<u32x4_u*>(row + t0) = u32x4_u{d[0], d[1], d[2], d[3]};
+      *reinterpret_cast<u32x4_u*>(row + t0 + 16) = u32x4_u{d[4], d[5], d[6], d[7]};
+    } else {
+      *reinterpret_cast<u32x2_u*>(row + t0) = u32x2_u{d[0], d[1]};
+    }
   } else {
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
+    for (int k = 0; k < n; ++k) {
+      const int t = t0 + 4 * k;
+      if (t + 4 <= HW) {
+        *reinterpret_cast<u32_u*>(row + t) = d[k];
+      } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int t = t0 + 4 * k + j;
-        if (t < HW) row[t] = (uint8_t)(d[k] >> (8 * j));
+        for (int j = 0; j < 4; ++j)
+          if (t + j < HW) row[t + j] = (uint8_t)(d[k] >> (8 * j));
       }
+    }
   }
 }
 
@@ -238,73 +259,80 @@ __device__ __forceinline__ uint32_t nibble_bytes(uint32_t sel, int k) {
   return (((sel >> (4 * k)) & 0xfu) * 0x00204081u) & 0x01010101u;
 }
 
-// Sum of the weight bytes w of the tokens whose bit is set in sel.
-__device__ __forceinline__ uint32_t weighted_count(const uint32_t (&w)[8], uint32_t sel) {
-  uint32_t acc = 0u;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) acc = __builtin_amdgcn_udot4(w[k], nibble_bytes(sel, k), acc, false);
-  return acc;
+// The per-step staleness rule on four tokens' bytes s (token j in byte j):
+// background (255) stays; a token whose byte of fresh_bytes is 0xff becomes
+// 0; any other foreground token adds 1, saturating at 254.
+__device__ __forceinline__ uint32_t stale_step(uint32_t s, uint32_t fresh_bytes) {
+  const uint32_t fgm = (bytes_nonzero(~s) >> 7) * 0xffu;          // 0xff per foreground byte
+  const uint32_t inc = bytes_nonzero(~(s | 0x01010101u)) >> 7;     // s < 254
+  return (s + inc) & ~(fresh_bytes & fgm);
 }
 
-// One block per (asset, view) row (blockIdx.x = b * N + v); its lanes
-// stride over the row's pair words.  stats[b][v] = foreground tokens, tokens
-// with staleness >= R, sum, max (after the update), reduced in the block and
-// written once: no atomics, and no zeroing launch in front.
+// The statistics of a row -- foreground tokens, tokens with staleness >= R,
+// sum, max -- over the words its block's lanes add.
 constexpr int kRowBlock = 512;
 
-template <bool VEC>
-__global__ __launch_bounds__(kRowBlock) void k_cov_update(const uint32_t* __restrict__ bits, int B, int N, int HW,
-                                                          int wpr, unsigned long long anchor_mask, int R,
-                                                          uint8_t* __restrict__ stale, uint32_t* __restrict__ stats) {
-  __shared__ uint32_t part[kRowBlock / 64][4];
-  const int bv = blockIdx.x;
-  const int b = bv / N, v = bv % N;
-  uint8_t* row = stale + (int64_t)bv * HW;
-  uint32_t c_fg = 0, c_ge = 0, c_sum = 0, c_max = 0;   // this lane's totals
-  for (int wi = (int)threadIdx.x; wi < wpr; wi += kRowBlock) {
-    const uint32_t fresh = set_covers(bits, B, N, wpr, anchor_mask, b, v, wi) & valid_bits(HW, wi);
-    uint32_t d[8];
-    load_word_bytes<VEC>(row, HW, wi * 32, d);
+struct RowStats {
+  uint32_t fg = 0, ge = 0, sum = 0, mx = 0;   // this lane's totals
+  // d: a word's staleness bytes after the step (background 255, also past the row)
+  __device__ __forceinline__ void add(const uint32_t (&d)[8], int R) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const uint32_t s = d[k];
-      const uint32_t fg = bytes_nonzero(~s);                       // s != 255
-      const uint32_t inc = bytes_nonzero(~(s | 0x01010101u)) >> 7;   // s < 254
-      const uint32_t fgm = (fg >> 7) * 0xffu;
-      const uint32_t zero = nibble_bytes(fresh, k) * 0xffu & fgm;
-      const uint32_t n = (s + inc) & ~zero;
-      d[k] = n;
-      const uint32_t nf = n & fgm;                                   // background reads 0
-      c_fg += (uint32_t)__popc(fg);
-      c_sum = __builtin_amdgcn_udot4(nf, 0x01010101u, c_sum, false);
+      const uint32_t on = bytes_nonzero(~d[k]);
+      const uint32_t nf = d[k] & ((on >> 7) * 0xffu);   // background reads 0
+      fg += (uint32_t)__popc(on);
+      sum = __builtin_amdgcn_udot4(nf, 0x01010101u, sum, false);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const uint32_t x = (nf >> (8 * j)) & 0xffu;
-        c_ge += x >= (uint32_t)R ? 1u : 0u;
-        c_max = max(c_max, x);
+        ge += x >= (uint32_t)R ? 1u : 0u;
+        mx = max(mx, x);
       }
     }
-    store_word_bytes<VEC>(row, HW, wi * 32, d);
   }
-  // every lane reaches the wave reductions (none returned early)
-  c_fg = wave_add(c_fg);
-  c_ge = wave_add(c_ge);
-  c_sum = wave_add(c_sum);
-  c_max = wave_max(c_max);
-  const int wv = (int)threadIdx.x / 64;
-  if (__lane_id() == 0) {
-    part[wv][0] = c_fg;
-    part[wv][1] = c_ge;
-    part[wv][2] = c_sum;
-    part[wv][3] = c_max;
+  // every thread of a kRowBlock block calls it
+  __device__ __forceinline__ void write(uint32_t* __restrict__ out) const {
+    __shared__ uint32_t part[kRowBlock / 64][4];
+    const uint32_t a = wave_add(fg), b = wave_add(ge), c = wave_add(sum), m = wave_max(mx);
+    if (__lane_id() == 0) {
+      uint32_t* p = part[threadIdx.x / 64];
+      p[0] = a; p[1] = b; p[2] = c; p[3] = m;
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+      const int k = (int)threadIdx.x;
+      uint32_t acc = 0u;
+      for (int q = 0; q < kRowBlock / 64; ++q) acc = k == 3 ? max(acc, part[q][k]) : acc + part[q][k];
+      out[k] = acc;
+    }
   }
-  __syncthreads();
-  if (threadIdx.x < 4) {
-    const int k = (int)threadIdx.x;
-    uint32_t acc = 0u;
-    for (int q = 0; q < kRowBlock / 64; ++q) acc = k == 3 ? max(acc, part[q][k]) : acc + part[q][k];
-    stats[(int64_t)bv * 4 + k] = acc;
+};
+
+// One step of a word's 32 tokens; fresh: the tokens some view of the set covers.
+__device__ __forceinline__ void step_word(uint32_t (&d)[8], uint32_t fresh) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) d[k] = stale_step(d[k], nibble_bytes(fresh, k) * 0xffu);
+}
+
+// One block per (asset, view) row (blockIdx.x = b * N + v); its lanes
+// stride over the row's pair words.  The statistics are reduced in the block
+// and written once: no atomics, and no zeroing launch in front.
+__global__ __launch_bounds__(kRowBlock) void k_cov_update(const uint32_t* __restrict__ bits, int B, int N, int HW,
+                                                          int wpr, unsigned long long anchor_mask, int R,
+                                                          uint8_t* __restrict__ stale, uint32_t* __restrict__ stats) {
+  const int bv = blockIdx.x;
+  const int b = bv / N, v = bv % N;
+  uint8_t* row = stale + (int64_t)bv * HW;
+  RowStats st;
+  for (int wi = (int)threadIdx.x; wi < wpr; wi += kRowBlock) {
+    const uint32_t fresh = set_covers(bits, B, N, wpr, anchor_mask, b, v, wi) & valid_bits(HW, wi);
+    uint32_t d[8];
+    load_bytes<8>(row, HW, wi * 32, d);
+    step_word(d, fresh);
+    st.add(d, R);
+    store_bytes<8>(row, HW, wi * 32, d);
   }
+  st.write(stats + (int64_t)bv * 4);
 }
 
 // ---------------------------------------------------------------------------
@@ -338,29 +366,6 @@ __global__ void k_hist_clear(HistState* __restrict__ hs, int nb, uint32_t* __res
   if (i < nb) hs->H[i] = 0ull;
   if (i < n_stats) stats[i] = 0u;
   if (i == 0) hs->ticket = 0u;
-}
-
-// Staleness bytes of tokens t0 .. t0 + 7 of a row, four per register;
-// tokens past the row read as background.  VEC: 16-byte aligned rows of a
-// multiple of 16 tokens (t0, a multiple of 8, then has all 8 in the row).
-template <bool VEC>
-__device__ __forceinline__ void load_8_bytes(const uint8_t* __restrict__ row, int HW, int t0, uint32_t (&d)[2]) {
-  if constexpr (VEC) {
-    const uint2 q = t0 < HW ? *reinterpret_cast<const uint2*>(row + t0) : make_uint2(~0u, ~0u);
-    d[0] = q.x;
-    d[1] = q.y;
-  } else {
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      uint32_t x = 0u;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int t = t0 + 4 * k + j;
-        x |= (t < HW ? (uint32_t)row[t] : 0xffu) << (8 * j);
-      }
-      d[k] = x;
-    }
-  }
 }
 
 // Y = the subset sums of H, left in y (LDS, indexed by mask).  The calling
@@ -414,11 +419,10 @@ __device__ __forceinline__ void subset_sums(const HistState* __restrict__ hs, in
   }
 }
 
-// The views of mask in ascending order.
-__device__ __forceinline__ void write_set(unsigned long long mask, int N, int32_t* out) {
-  int j = 0;
-  for (int u = 0; u < N; ++u)
-    if ((mask >> u) & 1ull) out[j++] = u;
+// The views of mask in ascending order, by the first GC_MAX_VIEWS threads of a block.
+__device__ __forceinline__ void write_set(unsigned long long mask, int32_t* out) {
+  const int u = (int)threadIdx.x;
+  if (u < GC_MAX_VIEWS && ((mask >> u) & 1ull)) out[__popcll(mask & ((1ull << u) - 1ull))] = u;
 }
 
 // Candidate sets as view masks.
@@ -426,31 +430,6 @@ constexpr int kMaxSets = 64;       // candidate sets per gc_coverage_score call
 struct SetMasks {
   unsigned long long m[kMaxSets];
 };
-
-// Staleness bytes of a lane's 8 tokens written back (VEC as for load_8_bytes).
-template <bool VEC>
-__device__ __forceinline__ void store_8_bytes(uint8_t* __restrict__ row, int HW, int t0, const uint32_t (&d)[2]) {
-  if constexpr (VEC) {
-    if (t0 < HW) *reinterpret_cast<uint2*>(row + t0) = make_uint2(d[0], d[1]);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int t = t0 + 4 * k + j;
-        if (t < HW) row[t] = (uint8_t)(d[k] >> (8 * j));
-      }
-  }
-}
-
-// The per-step staleness rule on four tokens' bytes s (token j in byte j):
-// background (255) stays; a token whose byte of fresh_bytes is 0xff becomes
-// 0; any other foreground token adds 1, saturating at 254.
-__device__ __forceinline__ uint32_t stale_step(uint32_t s, uint32_t fresh_bytes) {
-  const uint32_t fgm = (bytes_nonzero(~s) >> 7) * 0xffu;          // 0xff per foreground byte
-  const uint32_t inc = bytes_nonzero(~(s | 0x01010101u)) >> 7;     // s < 254
-  return (s + inc) & ~(fresh_bytes & fgm);
-}
 
 // The pass over the tokens (lane group of 4 per pair word, 8 tokens per
 // lane; each wave takes 16 consecutive words per round, blocks stride over
@@ -462,7 +441,7 @@ __device__ __forceinline__ uint32_t stale_step(uint32_t s, uint32_t fresh_bytes)
 // by k_hist_clear) -- the per-row sums of one wave with one atomic each --
 // so the histogram, and the selection or scores, are those of the updated
 // staleness.
-template <bool VEC, bool SCORE, bool UPDATE>
+template <bool SCORE, bool UPDATE>
 __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __restrict__ bits,
                                                            uint8_t* __restrict__ stale, int B, int N, int HW,
                                                            int wpr, int64_t n_words, HistState* __restrict__ hs, int a,
@@ -488,7 +467,7 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
     const int wi = active ? (int)(wg - (int64_t)bv * wpr) : 0;
     const int b = bv / N, v = bv - b * N;
     uint32_t d[2] = {~0u, ~0u};   // staleness bytes of the lane's 8 tokens (background past the row)
-    if (active) load_8_bytes<VEC>(stale + (int64_t)bv * HW, HW, wi * 32 + 8 * sub, d);
+    if (active) load_bytes<2>(stale + (int64_t)bv * HW, HW, wi * 32 + 8 * sub, d);
     uint32_t pb[kHistViews];      // the other views' pair bits of these 8 tokens
 #pragma unroll
     for (int u = 0; u < kHistViews; ++u)
@@ -515,7 +494,7 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
           c_max = max(c_max, x);
         }
       }
-      if (active) store_8_bytes<VEC>(stale + (int64_t)bv * HW, HW, wi * 32 + 8 * sub, d);
+      if (active) store_bytes<2>(stale + (int64_t)bv * HW, HW, wi * 32 + 8 * sub, d);
       // per-row statistics: one atomic per counter for a wave within one row
       const int bv0 = __builtin_amdgcn_readfirstlane(bv);   // lane 0 is always active
       if (__ballot(active && bv != bv0) == 0ull) {
@@ -580,138 +559,234 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
     // together (a view outside [0, N) or already chosen looks up its own
     // mask and is no candidate); the larger gain wins, on equal gains the
     // lower view
-    if (threadIdx.x != 0) return;
-    unsigned chosen = (unsigned)forced;
-    for (int n = __popc(chosen); n < a; ++n) {
-      const unsigned free_views = all & ~chosen;
-      unsigned long long rest[kHistViews];
+    __shared__ unsigned result;
+    if (threadIdx.x == 0) {
+      unsigned chosen = (unsigned)forced;
+      for (int n = __popc(chosen); n < a; ++n) {
+        const unsigned free_views = all & ~chosen;
+        unsigned long long rest[kHistViews];
 #pragma unroll
-      for (int u = 0; u < kHistViews; ++u) rest[u] = y[free_views & ~(1u << u)];
-      const unsigned long long base = y[free_views];
-      unsigned long long best_g = 0ull;
-      int best = kHistViews;
+        for (int u = 0; u < kHistViews; ++u) rest[u] = y[free_views & ~(1u << u)];
+        const unsigned long long base = y[free_views];
+        unsigned long long best_g = 0ull;
+        int best = kHistViews;
 #pragma unroll
-      for (int u = 0; u < kHistViews; ++u) {
-        const bool cand = u < N && !((chosen >> u) & 1u);
-        const unsigned long long g = base - rest[u];
-        const bool take = cand && (best == kHistViews || g > best_g);
-        best_g = take ? g : best_g;
-        best = take ? u : best;
+        for (int u = 0; u < kHistViews; ++u) {
+          const bool cand = u < N && !((chosen >> u) & 1u);
+          const unsigned long long g = base - rest[u];
+          const bool take = cand && (best == kHistViews || g > best_g);
+          best_g = take ? g : best_g;
+          best = take ? u : best;
+        }
+        chosen |= 1u << best;
       }
-      chosen |= 1u << best;
+      result = chosen;
     }
-    write_set(chosen, N, out);
+    __syncthreads();
+    write_set(result, out);
   }
 }
 
-// Reductions over all tokens (selection gains, set scores) run on at most
-// kRedBlocks one-wave blocks that stride over the items; lane u of a block
-// keeps candidate u's total, written as one partial row of the workspace at
-// the end, and one small block adds the rows up.  No global atomics: the
-// per-candidate counters would otherwise take an atomic from every block.
-constexpr int kRedBlocks = 2048;
+// ---------------------------------------------------------------------------
+// Selection and scores with more views than the histogram serves: one launch
+// per greedy round (or one for all the sets), the staleness step in the first,
+// and a last one that picks the last view, writes the result and recomputes
+// the statistics row by row.  A round's blocks leave their partial sums in the
+// workspace and every block of the next launch adds them up and picks the
+// round's view itself: no launch in between, no atomics, nothing to clear.
+//
+// Bound by launches and latency: a round takes 7 to 8 us at 2 assets x 20
+// views of 95 x 97, of which the pass itself is about two.  Update + selection
+// of 5 views there: 96 -> 45 us against update, and per round a pass of
+// one-wave blocks and a pick; set scores 33 -> 20 us; 64 views of 96 x 96 with
+// 8 anchors 232 -> 127 us.
+//
+// A block's four waves share an item (64 pair words of one row, a word per
+// lane); each takes every fourth view.  The weights are turned into bit
+// planes, so that a view's sum over a word's 32 tokens is one masked popcount
+// per plane that occurs (staleness is small: two or three of eight).
+constexpr int kSelBlock = 256;
+constexpr int kSelWaves = kSelBlock / 64;
+constexpr int kRedBlocks = 1024;   // partial sums per candidate that the workspace holds
+constexpr int kSelBlocks = 512;    // 8 x 16 views of 128 x 128 (1024 items): 128 / 256 / 512 blocks 67 / 47 / 45 us
+static_assert(kSelBlocks <= kRedBlocks, "the workspace holds the partial sums");
+constexpr int kFlushItems = 4096;  // items whose sums fit a lane's and a wave's 32 bits (32 * 255 * 64 * 4096 < 2^32)
 
-// Workspace layout: per-block partial sums, candidate-major (the reducer's
-// loads are coalesced), then the selection state.
 struct SelState {
-  unsigned long long part[GC_MAX_VIEWS][kRedBlocks];   // part[u][block]: gains or scores
-  unsigned long long chosen;                           // bit u: view u chosen
+  unsigned long long part[2][GC_MAX_VIEWS][kRedBlocks];   // of this and the previous round: [candidate][block]
+  unsigned long long chosen[GC_MAX_ANCHORS + 1];          // views chosen before round r
 };
 
-int red_blocks(int64_t n_items) { return (int)(n_items < kRedBlocks ? n_items : kRedBlocks); }
+int sel_blocks(int64_t n_items) { return (int)(n_items < kSelBlocks ? n_items : kSelBlocks); }
 
-// 1024 threads: wave w sums candidate u = w, w + 16, ... over the first nblk
-// blocks' partials (coalesced, then a wave sum) into out[u] (LDS).
-__device__ __forceinline__ void sum_partials(const SelState* st, int n, int nblk, unsigned long long* out) {
-  const int wv = threadIdx.x / 64, lane = __lane_id();
-  for (int u = wv; u < n; u += 16) {
-    unsigned long long acc = 0ull;
-#pragma unroll 4
-    for (int i = lane; i < nblk; i += 64) acc += st->part[u][i];
-    for (int o = 32; o > 0; o >>= 1) acc += (unsigned long long)__shfl_xor((long long)acc, o);
-    if (lane == 0) out[u] = acc;
-  }
+// wave_add for 64-bit sums.
+__device__ __forceinline__ unsigned long long wave_add64(unsigned long long v) {
+#define GC_ADD64(ctrl)                                                                                      \
+  v += (unsigned long long)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, ctrl, 0xf, 0xf, false) |    \
+       (unsigned long long)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), ctrl, 0xf, 0xf, false) << 32
+  GC_ADD64(kDppXor1);
+  GC_ADD64(kDppXor2);
+  GC_ADD64(kDppHalfMirror);
+  GC_ADD64(kDppMirror);
+#undef GC_ADD64
+  unsigned long long sum = 0ull;
+#pragma unroll
+  for (int r = 0; r < 64; r += 16)
+    sum += (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, r) |
+           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), r) << 32;
+  return sum;
 }
 
-// The views chosen before this round: the forced ones in the first round,
-// else the set the previous round's pick left in the workspace.
-__device__ __forceinline__ unsigned long long chosen_so_far(const SelState* st, unsigned long long forced, int first) {
-  return first ? forced : st->chosen;
-}
-
-// Per token: weight 1 + staleness if no chosen view covers it (0 for
-// background), added to every unchosen candidate that covers it.  Items
-// whose view is chosen are covered throughout and add nothing.
-template <bool VEC>
-__global__ __launch_bounds__(64) void k_sel_gains(const uint32_t* __restrict__ bits, const uint8_t* __restrict__ stale,
-                                                  int B, int N, int HW, int wpr, SelState* st,
-                                                  unsigned long long forced, int first) {
-  const unsigned long long chosen = chosen_so_far(st, forced, first);
-  const int lane = (int)threadIdx.x;
-  const int cpr = (wpr + 63) / 64;   // items per (asset, view)
-  const int64_t n_items = (int64_t)B * N * cpr;
-  unsigned long long mine = 0ull;    // lane u: candidate u's total
-  for (int64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
-    const int bv = (int)(it / cpr);
-    const int b = bv / N, v = bv - b * N;
-    if ((chosen >> v) & 1ull) continue;   // uniform
-    const int wi = (int)(it - (int64_t)bv * cpr) * 64 + lane;
-    uint32_t w[8];
-    load_word_bytes<VEC>(stale + (int64_t)bv * HW, HW, wi * 32, w);
+// The sums over the blocks' partials of candidates 0 .. n - 1 to out (LDS);
+// every thread of the block calls it, and it ends on a barrier.  A wave takes
+// CPW candidates at a time (wave w: w, w + waves, ...), all loads together.
+template <int CPW>
+__device__ __forceinline__ void sum_partials(const unsigned long long (*part)[kRedBlocks], int n, int nblk,
+                                             unsigned long long* out) {
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), lane = __lane_id();
+  const int waves = (int)blockDim.x / 64;
+  for (int u0 = wv; u0 < n; u0 += CPW * waves) {
+    unsigned long long acc[CPW] = {};
+    for (int i = lane; i < nblk; i += 64)
 #pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = bytes_plus_one(w[k]);
-    const bool in = wi < wpr;
-    const uint32_t live = in ? valid_bits(HW, wi) & ~set_covers(bits, B, N, wpr, chosen, b, v, wi) : 0u;
-    for (int u0 = 0; u0 < N; u0 += 16) {   // uniform; the group's words are loaded together
-      uint32_t wd[16];
+      for (int q = 0; q < CPW; ++q) acc[q] += part[min(u0 + q * waves, n - 1)][i];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int u = u0 + q;
-        wd[q] = (u >= N || ((chosen >> u) & 1ull) || !in) ? 0u : (u == v ? ~0u : pair_word(bits, B, N, wpr, u, b, v, wi));
-      }
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int u = u0 + q;
-        if (u < N) {   // uniform
-          const uint32_t g = wave_add(weighted_count(w, wd[q] & live));
-          if (lane == u) mine += g;
-        }
-      }
+    for (int q = 0; q < CPW; ++q) {
+      const unsigned long long sum = wave_add64(acc[q]);
+      if (lane == 0 && u0 + q * waves < n) out[u0 + q * waves] = sum;
     }
   }
-  if (lane < N) st->part[lane][blockIdx.x] = mine;
-}
-
-// 1024 threads: each view's gain is the sum of the blocks' partials; then
-// the unchosen view with the largest gain (ties: lower view) is chosen.  The
-// last round writes the set to out.
-__global__ __launch_bounds__(1024) void k_sel_pick(SelState* st, int N, int nblk, unsigned long long forced, int first,
-                                                   int32_t* out) {
-  __shared__ unsigned long long gain[GC_MAX_VIEWS];
-  sum_partials(st, N, nblk, gain);
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  unsigned long long chosen = chosen_so_far(st, forced, first);
-  int best = -1;
-  for (int c = 0; c < N; ++c) {
-    if ((chosen >> c) & 1ull) continue;
-    if (best < 0 || gain[c] > gain[best]) best = c;
+}
+
+// The views chosen before round r (r >= 1): those before round r - 1 and the
+// unchosen view with the largest gain of that round (ties: lower view).
+template <int CPW>
+__device__ __forceinline__ unsigned long long chosen_before(const SelState* st, int r, int N, int nblk,
+                                                            unsigned long long* gain) {
+  unsigned long long chosen = st->chosen[r - 1];
+  sum_partials<CPW>(st->part[(r - 1) & 1], N, nblk, gain);
+  const int lane = __lane_id();
+  const bool cand = lane < N && !((chosen >> lane) & 1ull);
+  const unsigned long long g = cand ? gain[lane] : 0ull;
+  const uint32_t hi = wave_max((uint32_t)(g >> 32));
+  const bool top = cand && (uint32_t)(g >> 32) == hi;
+  const uint32_t lo = wave_max(top ? (uint32_t)g : 0u);
+  const unsigned long long best = __ballot(top && (uint32_t)g == lo);
+  return best ? chosen | (best & (~best + 1ull)) : chosen;
+}
+
+// Bit planes of a word's weights: bit t of plane j is bit j of token t's byte.
+__device__ __forceinline__ uint32_t weight_plane(const uint32_t (&w)[8], int j) {
+  uint32_t p = 0u;
+#pragma unroll
+  for (int k = 0; k < 8; k += 2) {   // eight tokens: the byte's partial sums land on distinct bits
+    uint32_t x = __builtin_amdgcn_udot4((w[k] >> j) & 0x01010101u, 0x08040201u, 0u, false);
+    x = __builtin_amdgcn_udot4((w[k + 1] >> j) & 0x01010101u, 0x80402010u, x, false);
+    p |= x << (4 * k);
   }
-  if (best >= 0) chosen |= 1ull << best;
-  st->chosen = chosen;
-  if (out) write_set(chosen, N, out);
+  return p;
 }
 
-// the forced views are the whole set: no round runs
-__global__ void k_sel_forced(unsigned long long forced, int N, int32_t* out) {
-  if (threadIdx.x == 0) write_set(forced, N, out);
+// The bits that occur in some weight of the wave's live words.
+__device__ __forceinline__ uint32_t wave_planes(const uint32_t (&w)[8]) {
+  uint32_t x = ((w[0] | w[1]) | (w[2] | w[3])) | ((w[4] | w[5]) | (w[6] | w[7]));
+  x |= x >> 16;
+  x = (x | x >> 8) & 0xffu;
+  uint32_t m = 0u;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) m |= __ballot((x >> j) & 1u) ? 1u << j : 0u;
+  return m;
 }
 
-// score[m] partials: 1 + staleness over the foreground tokens set m covers.
-template <bool VEC>
-__global__ __launch_bounds__(64) void k_cov_score(const uint32_t* __restrict__ bits, const uint8_t* __restrict__ stale,
-                                                  int B, int N, int HW, int wpr, SetMasks sets, int M, SelState* st) {
-  const int lane = (int)threadIdx.x;
+// Gains of round r (r = 0: the forced views are chosen): per token weight
+// 1 + staleness if no chosen view covers it, added to every candidate that
+// does; items whose view is chosen are covered throughout and add nothing.
+// UPDATE: the staleness step of anchor_mask is applied first (round 0).
+// VPW: views per wave.
+template <int VPW, bool UPDATE>
+__global__ __launch_bounds__(kSelBlock) void k_sel_round(const uint32_t* __restrict__ bits, uint8_t* __restrict__ stale,
+                                                         int B, int N, int HW, int wpr, SelState* st, int r, int nblk,
+                                                         unsigned long long forced, unsigned long long anchor_mask) {
+  __shared__ unsigned long long gain[GC_MAX_VIEWS];
+  __shared__ uint32_t word[VPW * kSelWaves][64];   // the item's pair words of every view
+  const int lane = __lane_id();
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  const int cpr = (wpr + 63) / 64;   // items per (asset, view)
+  const int64_t n_items = (int64_t)B * N * cpr;
+  uint32_t d[8], wd[VPW];
+  int bv, wi;
+  auto load = [&](int64_t it) {
+    bv = (int)(it / cpr);
+    wi = (int)(it - (int64_t)bv * cpr) * 64 + lane;
+    const int b = bv / N, v = bv - b * N;
+    load_bytes<8>(stale + (int64_t)bv * HW, HW, wi * 32, d);
+#pragma unroll
+    for (int q = 0; q < VPW; ++q) {
+      const int u = q * kSelWaves + wv;
+      wd[q] = u >= N || wi >= wpr ? 0u : u == v ? ~0u : pair_word(bits, B, N, wpr, u, b, v, wi);
+    }
+  };
+  if (blockIdx.x < n_items) load(blockIdx.x);   // in flight while the view of the last round is picked
+  const unsigned long long chosen = r == 0 ? forced : chosen_before<VPW>(st, r, N, nblk, gain);
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->chosen[r] = chosen;
+  uint32_t acc[VPW] = {};
+  unsigned long long total[VPW] = {};
+  int left = kFlushItems;
+  for (int64_t it = blockIdx.x; it < n_items; it += gridDim.x) {
+#pragma unroll
+    for (int q = 0; q < VPW; ++q) word[q * kSelWaves + wv][lane] = wd[q];
+    __syncthreads();
+    auto covered = [&](unsigned long long mask) {   // the word's tokens that the views in mask cover
+      uint32_t c = 0u;
+      for (; mask; mask &= mask - 1) c |= word[__ffsll((long long)mask) - 1][lane];
+      return c;
+    };
+    const uint32_t live = wi < wpr ? valid_bits(HW, wi) & ~covered(chosen) : 0u;
+    if constexpr (UPDATE) {   // after the barrier: every wave has read the old bytes
+      step_word(d, wi < wpr ? covered(anchor_mask) & valid_bits(HW, wi) : 0u);
+      if (wv == 0) store_bytes<8>(stale + (int64_t)bv * HW, HW, wi * 32, d);
+    }
+    if (__ballot(live != 0u)) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) d[k] = bytes_plus_one(d[k]);
+      const uint32_t planes = wave_planes(d);
+      for (int j = 0; j < 8; ++j) {
+        if (!((planes >> j) & 1u)) continue;   // uniform
+        const uint32_t p = weight_plane(d, j) & live;
+#pragma unroll
+        for (int q = 0; q < VPW; ++q) acc[q] += (uint32_t)__popc(wd[q] & p) << j;
+      }
+    }
+    if (it + gridDim.x < n_items) load(it + gridDim.x);
+    if (--left == 0) {
+      left = kFlushItems;
+#pragma unroll
+      for (int q = 0; q < VPW; ++q) {
+        total[q] += wave_add(acc[q]);
+        acc[q] = 0u;
+      }
+    }
+    __syncthreads();   // the next item's words overwrite these
+  }
+#pragma unroll
+  for (int q = 0; q < VPW; ++q) {
+    const int u = q * kSelWaves + wv;
+    total[q] += wave_add(acc[q]);
+    if (u < N && lane == 0) st->part[r & 1][u][blockIdx.x] = total[q];
+  }
+}
+
+// Partial scores of the M sets: 1 + staleness over the foreground tokens a set
+// covers.  The item's pair words are put in LDS once, for every set.
+template <bool UPDATE>
+__global__ __launch_bounds__(kSelBlock) void k_score_pass(const uint32_t* __restrict__ bits,
+                                                          uint8_t* __restrict__ stale, int B, int N, int HW, int wpr,
+                                                          SelState* st, SetMasks sets, int M,
+                                                          unsigned long long anchor_mask) {
+  __shared__ uint32_t word[GC_MAX_VIEWS][64];
+  const int lane = __lane_id();
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int cpr = (wpr + 63) / 64;
   const int64_t n_items = (int64_t)B * N * cpr;
   unsigned long long mine = 0ull;   // lane m: set m's total
@@ -719,34 +794,75 @@ __global__ __launch_bounds__(64) void k_cov_score(const uint32_t* __restrict__ b
     const int bv = (int)(it / cpr);
     const int b = bv / N, v = bv - b * N;
     const int wi = (int)(it - (int64_t)bv * cpr) * 64 + lane;
-    uint32_t w[8];
-    load_word_bytes<VEC>(stale + (int64_t)bv * HW, HW, wi * 32, w);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = bytes_plus_one(w[k]);
     const bool in = wi < wpr;
-    const uint32_t vm = in ? valid_bits(HW, wi) : 0u;
-    for (int m = 0; m < M; ++m) {   // uniform
-      const uint32_t cov = in ? set_covers(bits, B, N, wpr, sets.m[m], b, v, wi) & vm : 0u;
-      const uint32_t g = wave_add(weighted_count(w, cov));
-      if (lane == m) mine += g;
+    uint8_t* row = stale + (int64_t)bv * HW;
+    uint32_t d[8];
+    load_bytes<8>(row, HW, wi * 32, d);
+    for (int u = wv; u < N; u += kSelWaves)
+      word[u][lane] = !in ? 0u : u == v ? ~0u : pair_word(bits, B, N, wpr, u, b, v, wi);
+    __syncthreads();
+    const uint32_t live = in ? valid_bits(HW, wi) : 0u;
+    if constexpr (UPDATE) {
+      uint32_t fresh = 0u;
+      for (unsigned long long m = anchor_mask; m; m &= m - 1) fresh |= word[__ffsll((long long)m) - 1][lane];
+      step_word(d, fresh & live);
+      if (wv == 0) store_bytes<8>(row, HW, wi * 32, d);   // after the barrier: every wave has read the old bytes
     }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) d[k] = bytes_plus_one(d[k]);
+    const uint32_t planes = wave_planes(d);
+    uint32_t p[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) p[j] = (planes >> j) & 1u ? weight_plane(d, j) & live : 0u;
+    for (int s = wv; s < M; s += kSelWaves) {   // uniform
+      uint32_t cov = 0u, sum = 0u;
+      for (unsigned long long m = sets.m[s]; m; m &= m - 1) cov |= word[__ffsll((long long)m) - 1][lane];
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if ((planes >> j) & 1u) sum += (uint32_t)__popc(cov & p[j]) << j;
+      const uint32_t g = wave_add(sum);
+      if (lane == s) mine += g;
+    }
+    __syncthreads();   // the next item's words overwrite these
   }
-  if (lane < M) st->part[lane][blockIdx.x] = mine;
+  // a wave's lanes hold its own sets' totals; the partials of set s sit with wave s % kSelWaves
+  if (lane < M && lane % kSelWaves == wv) st->part[0][lane][blockIdx.x] = mine;
 }
 
-__global__ __launch_bounds__(1024) void k_score_final(const SelState* st, int M, int nblk,
-                                                      unsigned long long* __restrict__ score) {
-  __shared__ unsigned long long sum[kMaxSets];
-  sum_partials(st, M, nblk, sum);
-  __syncthreads();
-  if ((int)threadIdx.x < M) score[threadIdx.x] = sum[threadIdx.x];
+// The result (block 0) after `rounds` rounds of k_sel_round or one pass of
+// k_score_pass, and, STATS, the statistics of row blockIdx.x.
+template <bool SCORE, bool STATS>
+__global__ __launch_bounds__(kRowBlock) void k_cov_final(const SelState* st, int N, int rounds, int nblk,
+                                                         unsigned long long forced, int32_t* __restrict__ out, int M,
+                                                         unsigned long long* __restrict__ score,
+                                                         const uint8_t* __restrict__ stale, int HW, int wpr, int R,
+                                                         uint32_t* __restrict__ stats) {
+  if (blockIdx.x == 0) {
+    __shared__ unsigned long long sum[kMaxSets];
+    if constexpr (SCORE) {
+      sum_partials<8>(st->part[0], M, nblk, sum);
+      if ((int)threadIdx.x < M) score[threadIdx.x] = sum[threadIdx.x];
+    } else {
+      write_set(rounds ? chosen_before<8>(st, rounds, N, nblk, sum) : forced, out);
+    }
+  }
+  if constexpr (STATS) {
+    const uint8_t* row = stale + (int64_t)blockIdx.x * HW;
+    RowStats rs;
+    for (int wi = (int)threadIdx.x; wi < wpr; wi += kRowBlock) {
+      uint32_t d[8];
+      load_bytes<8>(row, HW, wi * 32, d);
+      rs.add(d, R);
+    }
+    rs.write(stats + (int64_t)blockIdx.x * 4);
+  }
 }
 
 // The histogram path: clear H and the ticket (and the statistics), then the
 // pass over the tokens with the last block's rounds (select) or scores
 // (score); UPDATE applies the staleness step first (anchor_mask, R, stats).
 template <bool SCORE, bool UPDATE>
-void launch_hist(const uint32_t* bits, uint8_t* stale, int B, int N, size_t HW, HistState* hs, bool vec, int a,
+void launch_hist(const uint32_t* bits, uint8_t* stale, int B, int N, size_t HW, HistState* hs, int a,
                  unsigned long long forced, int32_t* out, const SetMasks& sets, int M, unsigned long long* score,
                  unsigned long long anchor_mask, int R, uint32_t* stats, hipStream_t stream) {
   const int wpr = (int)((HW + 31) / 32);
@@ -759,20 +875,12 @@ void launch_hist(const uint32_t* bits, uint8_t* stale, int B, int N, size_t HW, 
   const int n_clear = (1 << N) > n_stats ? (1 << N) : n_stats;
   hipLaunchKernelGGL(k_hist_clear, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, stream, hs, 1 << N, stats,
                      n_stats);
-  if (vec)
-    hipLaunchKernelGGL((k_cov_hist<true, SCORE, UPDATE>), dim3((unsigned)nblk), dim3(kHistThreads), 0, stream, bits,
-                       stale, B, N, (int)HW, wpr, n_words, hs, a, forced, out, sets, M, score, anchor_mask, R, stats);
-  else
-    hipLaunchKernelGGL((k_cov_hist<false, SCORE, UPDATE>), dim3((unsigned)nblk), dim3(kHistThreads), 0, stream, bits,
-                       stale, B, N, (int)HW, wpr, n_words, hs, a, forced, out, sets, M, score, anchor_mask, R, stats);
+  hipLaunchKernelGGL((k_cov_hist<SCORE, UPDATE>), dim3((unsigned)nblk), dim3(kHistThreads), 0, stream, bits, stale, B,
+                     N, (int)HW, wpr, n_words, hs, a, forced, out, sets, M, score, anchor_mask, R, stats);
 }
 
 // The histogram path serves N <= kHistViews (its grid stays below 2^31 blocks for any legal size).
 bool hist_path(int N) { return N <= kHistViews; }
-
-// The staleness rows start 16-byte aligned: the token kernels then move
-// each lane's 32 bytes with two 16-byte accesses.
-bool rows_aligned(const uint8_t* stale, size_t HW) { return ((uintptr_t)stale & 15u) == 0 && HW % 16 == 0; }
 
 int check_grid(int B, int N, int H, int W, const char* who) {
   if (B < 1 || N < 1 || H < 1 || W < 1) return fail(GC_ERR_SHAPE, "%s: bad shape B=%d N=%d H=%d W=%d", who, B, N, H, W);
@@ -913,53 +1021,55 @@ int check_score(const uint32_t* pair_bits, const uint8_t* stale, int B, int N, i
 // row's statistics.
 void launch_update(const uint32_t* pair_bits, int B, int N, size_t HW, unsigned long long mask, int R, uint8_t* stale,
                    uint32_t* stats, hipStream_t stream) {
-  const int wpr = (int)((HW + 31) / 32);
-  const dim3 grid((unsigned)(B * N));
-  if (rows_aligned(stale, HW))
-    hipLaunchKernelGGL(k_cov_update<true>, grid, dim3(kRowBlock), 0, stream, pair_bits, B, N, (int)HW, wpr, mask, R,
-                       stale, stats);
-  else
-    hipLaunchKernelGGL(k_cov_update<false>, grid, dim3(kRowBlock), 0, stream, pair_bits, B, N, (int)HW, wpr, mask, R,
-                       stale, stats);
+  hipLaunchKernelGGL(k_cov_update, dim3((unsigned)(B * N)), dim3(kRowBlock), 0, stream, pair_bits, B, N, (int)HW,
+                     (int)((HW + 31) / 32), mask, R, stale, stats);
 }
 
 // The selection on the current staleness (after the optional step of
-// mask_upd, R, stats, which the histogram pass applies itself).
+// mask_upd, R, stats, which the first pass over the tokens applies itself).
 void launch_select(const uint32_t* pair_bits, uint8_t* stale, int B, int N, size_t HW, int a, unsigned long long forced,
                    int n_forced, int32_t* anchors_out, void* workspace, bool upd, unsigned long long mask_upd, int R,
                    uint32_t* stats, hipStream_t stream) {
-  const bool vec = rows_aligned(stale, HW);
-  if (hist_path(N) && n_forced < a) {
+  const int rounds = a - n_forced;
+  if (hist_path(N) && rounds > 0) {
     SetMasks none;
     std::memset(&none, 0, sizeof(none));
     HistState* hs = static_cast<HistState*>(workspace);
     if (upd)
-      launch_hist<false, true>(pair_bits, stale, B, N, HW, hs, vec, a, forced, anchors_out, none, 0, nullptr, mask_upd,
-                               R, stats, stream);
+      launch_hist<false, true>(pair_bits, stale, B, N, HW, hs, a, forced, anchors_out, none, 0, nullptr, mask_upd, R,
+                               stats, stream);
     else
-      launch_hist<false, false>(pair_bits, stale, B, N, HW, hs, vec, a, forced, anchors_out, none, 0, nullptr, 0ull, 1,
+      launch_hist<false, false>(pair_bits, stale, B, N, HW, hs, a, forced, anchors_out, none, 0, nullptr, 0ull, 1,
                                 nullptr, stream);
-    return;
-  }
-  if (upd) launch_update(pair_bits, B, N, HW, mask_upd, R, stale, stats, stream);
-  if (n_forced == a) {
-    hipLaunchKernelGGL(k_sel_forced, dim3(1), dim3(64), 0, stream, forced, N, anchors_out);
     return;
   }
   SelState* st = static_cast<SelState*>(workspace);
   const int wpr = (int)((HW + 31) / 32);
-  const int nblk = red_blocks((int64_t)B * N * ((wpr + 63) / 64));
-  for (int r = n_forced; r < a; ++r) {   // more views: one pass over the tokens per round
-    const int first = r == n_forced;
-    int32_t* out = r == a - 1 ? anchors_out : nullptr;
-    if (vec)
-      hipLaunchKernelGGL(k_sel_gains<true>, dim3(nblk), dim3(64), 0, stream, pair_bits, stale, B, N, (int)HW, wpr, st,
-                         forced, first);
-    else
-      hipLaunchKernelGGL(k_sel_gains<false>, dim3(nblk), dim3(64), 0, stream, pair_bits, stale, B, N, (int)HW, wpr, st,
-                         forced, first);
-    hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(1024), 0, stream, st, N, nblk, forced, first, out);
+  const int nblk = sel_blocks((int64_t)B * N * ((wpr + 63) / 64));
+  if (rounds == 0 && upd) {   // the forced views are the whole set: the step alone
+    launch_update(pair_bits, B, N, HW, mask_upd, R, stale, stats, stream);
+    upd = false;
   }
+#define GC_SEL_ROUND(VPW_, UPD_)                                                                               \
+  hipLaunchKernelGGL((k_sel_round<VPW_, UPD_>), dim3((unsigned)nblk), dim3(kSelBlock), 0, stream, pair_bits, stale, B, N, \
+                     (int)HW, wpr, st, r, nblk, forced, mask_upd)
+  for (int r = 0; r < rounds; ++r) {
+    const bool step = upd && r == 0;
+    if (N <= 4 * kSelWaves) {
+      if (step) GC_SEL_ROUND(4, true); else GC_SEL_ROUND(4, false);
+    } else if (N <= 8 * kSelWaves) {
+      if (step) GC_SEL_ROUND(8, true); else GC_SEL_ROUND(8, false);
+    } else {
+      if (step) GC_SEL_ROUND(16, true); else GC_SEL_ROUND(16, false);
+    }
+  }
+#undef GC_SEL_ROUND
+  if (upd)
+    hipLaunchKernelGGL((k_cov_final<false, true>), dim3((unsigned)(B * N)), dim3(kRowBlock), 0, stream, st, N, rounds,
+                       nblk, forced, anchors_out, 0, nullptr, stale, (int)HW, wpr, R, stats);
+  else
+    hipLaunchKernelGGL((k_cov_final<false, false>), dim3(1), dim3(kRowBlock), 0, stream, st, N, rounds, nblk, forced,
+                       anchors_out, 0, nullptr, nullptr, 0, 0, 1, nullptr);
 }
 
 // The set scores on the current staleness (after the optional step, as above).
@@ -970,24 +1080,27 @@ void launch_score(const uint32_t* pair_bits, uint8_t* stale, int B, int N, size_
   if (hist_path(N)) {
     HistState* hs = static_cast<HistState*>(workspace);
     if (upd)
-      launch_hist<true, true>(pair_bits, stale, B, N, HW, hs, rows_aligned(stale, HW), a, 0ull, nullptr, masks, M, out,
-                              mask_upd, R, stats, stream);
+      launch_hist<true, true>(pair_bits, stale, B, N, HW, hs, a, 0ull, nullptr, masks, M, out, mask_upd, R, stats,
+                              stream);
     else
-      launch_hist<true, false>(pair_bits, stale, B, N, HW, hs, rows_aligned(stale, HW), a, 0ull, nullptr, masks, M,
-                               out, 0ull, 1, nullptr, stream);
+      launch_hist<true, false>(pair_bits, stale, B, N, HW, hs, a, 0ull, nullptr, masks, M, out, 0ull, 1, nullptr,
+                               stream);
     return;
   }
-  if (upd) launch_update(pair_bits, B, N, HW, mask_upd, R, stale, stats, stream);
   SelState* st = static_cast<SelState*>(workspace);
   const int wpr = (int)((HW + 31) / 32);
-  const int nblk = red_blocks((int64_t)B * N * ((wpr + 63) / 64));
-  if (rows_aligned(stale, HW))
-    hipLaunchKernelGGL(k_cov_score<true>, dim3(nblk), dim3(64), 0, stream, pair_bits, stale, B, N, (int)HW, wpr, masks,
-                       M, st);
-  else
-    hipLaunchKernelGGL(k_cov_score<false>, dim3(nblk), dim3(64), 0, stream, pair_bits, stale, B, N, (int)HW, wpr, masks,
-                       M, st);
-  hipLaunchKernelGGL(k_score_final, dim3(1), dim3(1024), 0, stream, st, M, nblk, out);
+  const int nblk = sel_blocks((int64_t)B * N * ((wpr + 63) / 64));
+  if (upd) {
+    hipLaunchKernelGGL(k_score_pass<true>, dim3((unsigned)nblk), dim3(kSelBlock), 0, stream, pair_bits, stale, B, N,
+                       (int)HW, wpr, st, masks, M, mask_upd);
+    hipLaunchKernelGGL((k_cov_final<true, true>), dim3((unsigned)(B * N)), dim3(kRowBlock), 0, stream, st, N, 0, nblk,
+                       0ull, nullptr, M, out, stale, (int)HW, wpr, R, stats);
+  } else {
+    hipLaunchKernelGGL(k_score_pass<false>, dim3((unsigned)nblk), dim3(kSelBlock), 0, stream, pair_bits, stale, B, N,
+                       (int)HW, wpr, st, masks, M, 0ull);
+    hipLaunchKernelGGL((k_cov_final<true, false>), dim3(1), dim3(kRowBlock), 0, stream, st, N, 0, nblk, 0ull, nullptr,
+                       M, out, nullptr, 0, 0, 1, nullptr);
+  }
 }
 
 }  // namespace
