@@ -12,6 +12,7 @@ library has not been built.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 from typing import Dict, List, Optional, Sequence, Tuple
@@ -70,7 +71,13 @@ class Sampler:
     beta_end: float = 0.02
 
     def c(self) -> _Sampler:
-        return _Sampler(self.kind, self.pred_out, self.T, 0, self.beta_start, self.beta_end)
+        return _sampler_struct(self.kind, self.pred_out, self.T, self.beta_start, self.beta_end)
+
+
+@functools.lru_cache(maxsize=64)
+def _sampler_struct(kind, pred_out, T, beta_start, beta_end) -> _Sampler:
+    """The C form of a sampler's (immutable) parameters; nothing writes to it."""
+    return _Sampler(kind, pred_out, T, 0, beta_start, beta_end)
 
 
 _LIB = None
@@ -151,9 +158,22 @@ def _check(rc: int, func: str) -> None:
         raise GeoCacheError(func, rc, lib().gc_last_error().decode(errors="replace"))
 
 
+def _current_raw_stream() -> int:
+    """Handle of torch's current stream on the current device, without the
+    Stream object that torch.cuda.current_stream() builds on the way (a few
+    microseconds of a step's host time)."""
+    if _RAW_STREAM is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _RAW_STREAM(torch._C._cuda_getDevice())
+
+
+# what torch's own generated code calls for the same purpose
+_RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None) if hasattr(torch._C, "_cuda_getDevice") else None
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _current_raw_stream()
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
@@ -173,6 +193,8 @@ def _keep(stream, tensors) -> None:
     """Tensors this binding allocated and handed to work on a side stream:
     tell torch's caching allocator, so that their memory is not given to
     current-stream work before the side stream's kernels are done with it."""
+    if stream is None:
+        return
     s = _side_stream(stream)
     if s is not None:
         for t in tensors:
@@ -188,13 +210,13 @@ def _after_side(stream) -> None:
 
 
 def _dev(t: torch.Tensor, name: str) -> int:
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
         raise ValueError(f"{name} must be a device tensor (got {t.device})")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return t.data_ptr()
+    raise ValueError(f"{name} must be contiguous")
 
 
 def _opt(t: Optional[torch.Tensor], name: str) -> Optional[int]:
@@ -209,9 +231,14 @@ def dtype_code(t: torch.Tensor) -> int:
     raise ValueError(f"latents must be float32 or bfloat16 (got {t.dtype})")
 
 
+# int32 array types by length (an array type made anew for each call costs
+# more than the array)
+_I32 = [ctypes.c_int32 * n for n in range(GC_MAX_VIEWS + 1)]
+
+
 def _anchors(anchors: Sequence[int]):
-    arr = (ctypes.c_int32 * len(anchors))(*[int(x) for x in anchors])
-    return arr, len(anchors)
+    n = len(anchors)
+    return (_I32[n] if n <= GC_MAX_VIEWS else ctypes.c_int32 * n)(*map(int, anchors)), n
 
 
 def camera_tensor(cams: Dict[str, np.ndarray], device="cuda") -> torch.Tensor:
@@ -894,17 +921,16 @@ def gc_schedule_forced_views(gap: Sequence[int], a: int, max_gap: int) -> List[i
 
 def gc_schedule_advance_gaps(gap: Sequence[int], views: Sequence[int], full: bool) -> List[int]:
     """The anchor gaps after a step that predicted `views` (all views if full)."""
-    N = len(gap)
-    g = (ctypes.c_int32 * max(N, 1))(*[int(x) for x in gap])
+    g, N = _anchors(gap)
     arr, n = _anchors(views)
     _check(lib().gc_schedule_advance_gaps(g, N, arr, n, int(bool(full))), "gc_schedule_advance_gaps")
-    return list(g[:N])
+    return g[:N]
 
 
 def gc_schedule_anchors(N: int, a: int, c: int) -> List[int]:
-    out = (ctypes.c_int32 * a)()
+    out = (_I32[a] if 0 <= a <= GC_MAX_VIEWS else ctypes.c_int32 * a)()
     _check(lib().gc_schedule_anchors(N, a, c, out), "gc_schedule_anchors")
-    return list(out)
+    return out[:a]
 
 
 def gc_schedule_full_steps(rule: int, S: int, E: int = 0) -> List[int]:
