@@ -30,6 +30,10 @@ template <int DT, int VEC> struct Codec {
   __device__ __forceinline__ static Raw load(const void* base, int64_t elem) {
     return *reinterpret_cast<const Raw*>(static_cast<const char*>(base) + elem * (DT == GC_F32 ? 4 : 2));
   }
+  // cached store: an output that the next call reads
+  __device__ __forceinline__ static void store(void* base, int64_t elem, const Raw& r) {
+    *reinterpret_cast<Raw*>(static_cast<char*>(base) + elem * (DT == GC_F32 ? 4 : 2)) = r;
+  }
   // streamed load / store: data touched exactly once per step.  The
   // nontemporal hint keeps it from displacing the gathered anchor tiles in L2.
   __device__ __forceinline__ static Raw load_stream(const void* base, int64_t elem) {

@@ -175,7 +175,9 @@ __device__ __forceinline__ void token_step(const TArgs& g, int b, int p, int cv,
     if (g.u.need_m2) CD::unpack(m2r, m2);
     if (g.u.need_m1) CD::unpack(m1r, m1);
     unipc_vec<VEC>(g.u, xin, m2, m1, x0f, xc, xn);
-    CD::store_stream(g.x_c, base, CD::pack(xc));
+    // x_c is the next step's x_prev: a cached store (8 x 12 views of 128 x 128
+    // x 16 bf16: 63.0 -> 60.7 us; x_next cached as well 62.0)
+    CD::store(g.x_c, base, CD::pack(xc));
     CD::store_stream(g.x_next, base, CD::pack(xn));
   }
 }
@@ -275,23 +277,33 @@ __global__ __launch_bounds__(kBlock) void k_reconstruct(const void* __restrict__
   if (model_out) CD::store_stream(model_out, i * VEC, CD::pack(mo));
 }
 
+// HBM-bound, four streams in and two out.  All loads are issued before any is
+// used, and the outputs, which the next step reads, are plain stores: 8 x 12
+// views of 128 x 128 x 16 bf16 51.5 -> 48.5 us (6.2 TB/s; 49.4 with
+// nontemporal stores; two or four vectors per lane 50.0 / 52.0, 512-lane
+// blocks 48.3).
 template <int DT, int VEC>
 __global__ __launch_bounds__(kBlock) void k_unipc(TArgs g, const void* __restrict__ m_k, int64_t n_vec) {
   using CD = Codec<DT, VEC>;
+  using Raw = typename CD::Raw;
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= n_vec) return;
+  Raw m2r, m1r;
+  const Raw xr = CD::load_stream(g.u.corr ? g.x_prev : g.x_t, i * VEC);
+  if (g.u.need_m2) m2r = CD::load_stream(g.m_km2, i * VEC);
+  if (g.u.need_m1) m1r = CD::load_stream(g.x0_prev, i * VEC);
+  const Raw mkr = CD::load_stream(m_k, i * VEC);
   float xin[VEC], m2[VEC], m1[VEC], mk[VEC], xc[VEC], xn[VEC];
-  CD::unpack(CD::load_stream(g.u.corr ? g.x_prev : g.x_t, i * VEC), xin);
 #pragma unroll
   for (int e = 0; e < VEC; ++e) m2[e] = m1[e] = 0.0f;
-  if (g.u.need_m2) CD::unpack(CD::load_stream(g.m_km2, i * VEC), m2);
-  if (g.u.need_m1) CD::unpack(CD::load_stream(g.x0_prev, i * VEC), m1);
-  CD::unpack(CD::load_stream(m_k, i * VEC), mk);
+  CD::unpack(xr, xin);
+  if (g.u.need_m2) CD::unpack(m2r, m2);
+  if (g.u.need_m1) CD::unpack(m1r, m1);
+  CD::unpack(mkr, mk);
   unipc_vec<VEC>(g.u, xin, m2, m1, mk, xc, xn);
-  CD::store_stream(g.x_c, i * VEC, CD::pack(xc));
-  CD::store_stream(g.x_next, i * VEC, CD::pack(xn));
+  CD::store(g.x_c, i * VEC, CD::pack(xc));
+  CD::store(g.x_next, i * VEC, CD::pack(xn));
 }
-
 
 // Validation shared by the transport entry points; fills g (except the
 // reconstruction coefficients and the fused-only pointers).
