@@ -8,10 +8,10 @@
 // foreground ones in token order and puts their positions side by side in
 // LDS; the operator then runs on full waves of them.
 //
-// 256 tokens per block: with 512 and 1024 fewer groups of 64 are partly
-// filled, but a dense block's chain of groups grows while its neighbours are
-// empty (8 assets x 12 views of 128 x 128: visibility pairs 35 / 55 / 73 us,
-// builder 22 / 34 / 43 us with 256 / 512 / 1024).
+// Small chunks: with larger ones fewer groups of 64 are partly filled, but a
+// dense block's chain of groups grows while its neighbours are empty (8 assets
+// x 12 views of 128 x 128, chunks of 128 / 256 / 512 / 1024 tokens: visibility
+// pairs 36 / 35 / 55 / 73 us, builder 18.7 / 21.6 / 34 / 43 us).
 #pragma once
 
 #include "gc_common.h"
@@ -19,20 +19,19 @@
 
 namespace gc {
 
-constexpr int kCompactTok = 256;                  // tokens per chunk: one per thread of the block
-constexpr int kCompactWaves = kCompactTok / 64;
-
-struct CompactLds {
-  float q[3][kCompactTok];      // positions of the chunk's foreground tokens, in token order
-  uint16_t at[kCompactTok];     // their tokens' offsets in the chunk
-  int32_t count[kCompactWaves];
+// A chunk of TOK tokens: one per thread of a block of TOK.
+template <int TOK> struct CompactLds {
+  float q[3][TOK];              // positions of the chunk's foreground tokens, in token order
+  uint16_t at[TOK];             // their tokens' offsets in the chunk
+  int32_t count[TOK / 64];
 };
 
 // Rank among the chunk's foreground tokens of this thread's token p0 +
 // threadIdx.x of the view map row [HW][3] (-1: background or past the view);
 // n_fg: the chunk's foreground count.  Every thread of the block must call
 // it; it ends on a barrier.
-__device__ __forceinline__ int compact_foreground(const float* __restrict__ row, int HW, int p0, CompactLds& s,
+template <int TOK>
+__device__ __forceinline__ int compact_foreground(const float* __restrict__ row, int HW, int p0, CompactLds<TOK>& s,
                                                   int* n_fg) {
   const int wv = (int)threadIdx.x / 64;
   const int p = p0 + (int)threadIdx.x;
@@ -44,7 +43,7 @@ __device__ __forceinline__ int compact_foreground(const float* __restrict__ row,
   __syncthreads();
   int before = 0, total = 0;
 #pragma unroll
-  for (int w = 0; w < kCompactWaves; ++w) {
+  for (int w = 0; w < TOK / 64; ++w) {
     const int c = s.count[w];
     before += w < wv ? c : 0;
     total += c;

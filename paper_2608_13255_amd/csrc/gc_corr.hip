@@ -23,6 +23,12 @@ namespace {
 // blocks; one that does not uses enough blocks to hide its load latency.
 constexpr int kBuildBlocksPerCU = 16;
 constexpr int kBuildBlocksPerCUStats = 4;
+// Tokens per chunk, and threads per block.  Groups of four lanes: 128 (8 assets
+// x 8 target views of 128 x 128 with 4 anchors 18.5 us; 64 20.0, 192 19.2, 256
+// 21.6).  With the counters, whose atomics grow with the blocks, 256 (21.6 us;
+// 192 25.5, 128 28.4), as with groups of eight lanes (3 assets x 10 target
+// views of 75 x 101 with 6 anchors 12.0 us; 128 13.7, 64 15.4).
+constexpr int build_tok(int group, bool count) { return group == 4 && !count ? 128 : 256; }
 
 struct BuildArgs {
   const float* pos;
@@ -50,10 +56,10 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return v;
 }
 
-// Bound by vector-ALU issue (12 of 22 us) and by the chain of a block's loads;
+// Bound by vector-ALU issue (12 of 18.5 us) and by the chain of a block's loads;
 // without the compaction a lane per (raster token, slot) took 24.6 us on 8
-// assets x 8 target views of 128 x 128 with 4 anchors (34 -> 22 us with the
-// counters).
+// assets x 8 target views of 128 x 128 with 4 anchors, now 18.5 (34 -> 21.6 us
+// with the counters).
 //
 // A block compacts the foreground tokens of a chunk of one target view, writes
 // the other tokens' zero words, and then gives each (compacted token, anchor
@@ -69,8 +75,9 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 // taps over all its chunks and adds them to the asset's counters once: few
 // blocks per asset keep the same-address atomics from serialising.
 template <int G, bool COUNT>
-__global__ __launch_bounds__(kCompactTok) void k_build(BuildArgs g) {
-  __shared__ CompactLds list;
+__global__ __launch_bounds__(build_tok(G, COUNT)) void k_build(BuildArgs g) {
+  constexpr int kTok = build_tok(G, COUNT);
+  __shared__ CompactLds<kTok> list;
   __shared__ gc_camera cam_lds[GC_MAX_ANCHORS];
   __shared__ int32_t view_lds[GC_MAX_ANCHORS];   // a lane's own slot: from LDS, not a per-lane kernel-argument load
   const int HW = g.H * g.W;
@@ -88,11 +95,11 @@ __global__ __launch_bounds__(kCompactTok) void k_build(BuildArgs g) {
   const int s = (int)threadIdx.x & (G - 1);      // anchor slot of this lane
   const int sc = s < g.a ? s : 0;
   const int gbase = lane & ~(G - 1);
-  const int n_chunks = (HW + kCompactTok - 1) / kCompactTok;
+  const int n_chunks = (HW + kTok - 1) / kTok;
   uint32_t c_pairs = 0, c_pix = 0, c_fg = 0;   // wave totals (uniform across the wave)
   uint32_t taps_lane = 0;                       // this lane's kept taps, summed over the wave at the end
   for (int chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
-    const int p0 = chunk * kCompactTok;
+    const int p0 = chunk * kTok;
     int n_fg;
     const int rank = compact_foreground(view, HW, p0, list, &n_fg);   // its barriers also order the cameras
     const int p = p0 + (int)threadIdx.x;
@@ -105,7 +112,7 @@ __global__ __launch_bounds__(kCompactTok) void k_build(BuildArgs g) {
       }
     }
     if (COUNT && threadIdx.x / 64 == 0) c_fg += (uint32_t)n_fg;
-    for (int i0 = 0; i0 < n_fg; i0 += kCompactTok / G) {
+    for (int i0 = 0; i0 < n_fg; i0 += kTok / G) {
       const int i = i0 + (int)threadIdx.x / G;
       const bool live = i < n_fg && s < g.a;
       const int ic = i < n_fg ? i : 0;
@@ -171,7 +178,7 @@ __global__ __launch_bounds__(kCompactTok) void k_build(BuildArgs g) {
     // blocks never straddle assets (grid y is per asset and target): the
     // block sums its waves' totals in LDS, one thread per counter adds them
     // to the asset's counters
-    __shared__ uint32_t part[kCompactWaves][4];
+    __shared__ uint32_t part[kTok / 64][4];
     const uint32_t c_taps = wave_sum(taps_lane);
     const int wv = (int)threadIdx.x / 64;
     if (lane == 0) {
@@ -183,7 +190,7 @@ __global__ __launch_bounds__(kCompactTok) void k_build(BuildArgs g) {
     __syncthreads();
     if (threadIdx.x < 4) {
       uint32_t sum = 0;
-      for (int w = 0; w < kCompactWaves; ++w) sum += part[w][threadIdx.x];
+      for (int w = 0; w < kTok / 64; ++w) sum += part[w][threadIdx.x];
       if (sum) atomicAdd(g.stats + (int64_t)b * 4 + threadIdx.x, sum);
     }
   }
@@ -243,23 +250,21 @@ extern "C" int gc_build_correspondence(const float* pos, const gc_camera* cams, 
   if (stats) hipLaunchKernelGGL(k_zero_u32, dim3((4 * B + 255) / 256), dim3(256), 0, stream, stats, 4 * B);
   if (NT > 0) {
     // x-blocks per (asset, target), from the launch size above
-    const int64_t chunks = ((int64_t)HW + kCompactTok - 1) / kCompactTok;
-    const int64_t per_cu = stats ? kBuildBlocksPerCUStats : kBuildBlocksPerCU;
-    int64_t bx = (per_cu * 256 + (int64_t)B * NT - 1) / ((int64_t)B * NT);
-    if (bx > chunks) bx = chunks;
-    if (bx < 1) bx = 1;
-    const dim3 grid((unsigned)bx, (unsigned)(B * NT)), block(kCompactTok);
+#define GC_BUILD(G_, COUNT_)                                                                                  \
+  do {                                                                                                        \
+    constexpr int tok = build_tok(G_, COUNT_);                                                                \
+    const int64_t chunks = ((int64_t)HW + tok - 1) / tok;                                                     \
+    const int64_t per_cu = COUNT_ ? kBuildBlocksPerCUStats : kBuildBlocksPerCU;                               \
+    int64_t bx = (per_cu * 256 + (int64_t)B * NT - 1) / ((int64_t)B * NT);                                    \
+    if (bx > chunks) bx = chunks;                                                                             \
+    hipLaunchKernelGGL((k_build<G_, COUNT_>), dim3((unsigned)bx, (unsigned)(B * NT)), dim3(tok), 0, stream, g); \
+  } while (0)
     if (a <= 4) {
-      if (stats)
-        hipLaunchKernelGGL((k_build<4, true>), grid, block, 0, stream, g);
-      else
-        hipLaunchKernelGGL((k_build<4, false>), grid, block, 0, stream, g);
+      if (stats) GC_BUILD(4, true); else GC_BUILD(4, false);
     } else {
-      if (stats)
-        hipLaunchKernelGGL((k_build<8, true>), grid, block, 0, stream, g);
-      else
-        hipLaunchKernelGGL((k_build<8, false>), grid, block, 0, stream, g);
+      if (stats) GC_BUILD(8, true); else GC_BUILD(8, false);
     }
+#undef GC_BUILD
   }
   return after_launch(stream, "gc_build_correspondence");
 }

@@ -60,6 +60,8 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
              max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
 }
 
+constexpr int kCompactTok = 256;   // tokens per chunk, and threads per block
+constexpr int kCompactWaves = kCompactTok / 64;
 constexpr int kPairBatch = 2;   // anchors whose tap loads a wave keeps in flight together (1: 45 us, 2 and 3: 35, 4: 39)
 
 // One block per chunk of kCompactTok tokens of a view (grid: x = chunk,
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(kCompactTok) void k_cov_pairs(const float* __restri
                                                            const float* __restrict__ bbox, int B, int N, int H, int W,
                                                            int wpr, uint32_t* __restrict__ bits) {
   constexpr int kWords = kCompactTok / 32;         // words of bits per chunk and anchor
-  __shared__ CompactLds s;
+  __shared__ CompactLds<kCompactTok> s;
   __shared__ unsigned long long seen[GC_MAX_VIEWS][kCompactTok / 64];   // ballots: [anchor][group]
   static_assert(sizeof(s.q) >= GC_MAX_VIEWS * kWords * 4, "the words take the positions' place");
   uint32_t(*words)[kWords] = reinterpret_cast<uint32_t(*)[kWords]>(&s.q[0][0]);   // [anchor][word], after the last pair
