@@ -32,6 +32,12 @@ namespace {
 constexpr int kBlock = 256;
 constexpr uint8_t kBackground = 255;
 
+// Unaligned vectors: the hardware reads and writes them at any byte, so a
+// row's bytes move in wide accesses whatever H * W and the buffer's address.
+typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32_u __attribute__((aligned(1)));
+
 // Wave-wide sum and maximum, returned wave-uniform; every lane of the wave
 // must be active.  Within each row of 16 lanes, DPP moves pair lane i with i
 // xor 1, i xor 2, 7 - i (within 8) and 15 - i, so every lane ends with its
@@ -149,11 +155,24 @@ __global__ __launch_bounds__(kCompactTok) void k_cov_pairs(const float* __restri
   }
 }
 
-__global__ void k_cov_init(const float* __restrict__ pos, int64_t n_tok, uint8_t* __restrict__ stale) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+// Four tokens per thread: three 16-byte loads (positions are 4-byte aligned)
+// and one 4-byte store; the last thread takes what is left one by one.
+__global__ __launch_bounds__(kBlock) void k_cov_init(const float* __restrict__ pos, int64_t n_tok,
+                                                     uint8_t* __restrict__ stale) {
+  typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4;
   if (i >= n_tok) return;
-  const float* P = pos + i * 3;
-  stale[i] = (finite_f(P[0]) && finite_f(P[1]) && finite_f(P[2])) ? 0 : kBackground;
+  const auto value = [](float x, float y, float z) -> uint32_t {
+    return finite_f(x) && finite_f(y) && finite_f(z) ? 0u : kBackground;
+  };
+  if (i + 4 <= n_tok) {
+    const f32x4_u* P = reinterpret_cast<const f32x4_u*>(pos + i * 3);
+    const f32x4_u a = P[0], b = P[1], c = P[2];
+    *reinterpret_cast<u32_u*>(stale + i) = value(a.x, a.y, a.z) | value(a.w, b.x, b.y) << 8 |
+                                           value(b.z, b.w, c.x) << 16 | value(c.y, c.z, c.w) << 24;
+  } else {
+    for (int64_t k = i; k < n_tok; ++k) stale[k] = (uint8_t)value(pos[3 * k], pos[3 * k + 1], pos[3 * k + 2]);
+  }
 }
 
 // The token kernels give each lane one pair word: 32 consecutive tokens of
@@ -182,12 +201,6 @@ __device__ __forceinline__ uint32_t valid_bits(int HW, int wi) {
   const int n = HW - wi * 32;
   return n >= 32 ? ~0u : (n <= 0 ? 0u : (1u << n) - 1u);
 }
-
-// Unaligned vectors: the hardware reads and writes them at any byte, so a
-// row's bytes move in wide accesses whatever H * W and the buffer's address.
-typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(1)));
-typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(1)));
-typedef uint32_t u32_u __attribute__((aligned(1)));
 
 // Staleness bytes of tokens t0 .. t0 + 4 n - 1 of a row, four per register
 // (token t0 + 4k + j in byte j of d[k]); tokens past the row read as
@@ -597,11 +610,11 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
 // workspace and every block of the next launch adds them up and picks the
 // round's view itself: no launch in between, no atomics, nothing to clear.
 //
-// Bound by launches and latency: a round takes 7 to 8 us at 2 assets x 20
+// Bound by launches and latency: a round takes about 6 us at 2 assets x 20
 // views of 95 x 97, of which the pass itself is about two.  Update + selection
-// of 5 views there: 96 -> 45 us against update, and per round a pass of
-// one-wave blocks and a pick; set scores 33 -> 20 us; 64 views of 96 x 96 with
-// 8 anchors 232 -> 127 us.
+// of 5 views there: 96 -> 38 us against update, and per round a pass of
+// one-wave blocks and a pick; set scores 33 -> 16 us; 64 views of 96 x 96 with
+// 8 anchors 232 -> 104 us.
 //
 // A block's four waves share an item (64 pair words of one row, a word per
 // lane); each takes every fourth view.  The weights are turned into bit
@@ -610,64 +623,41 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
 constexpr int kSelBlock = 256;
 constexpr int kSelWaves = kSelBlock / 64;
 constexpr int kRedBlocks = 1024;   // partial sums per candidate that the workspace holds
-constexpr int kSelBlocks = 512;    // 8 x 16 views of 128 x 128 (1024 items): 128 / 256 / 512 blocks 67 / 47 / 45 us
+constexpr int kSelBlocks = 512;    // 8 x 16 views of 128 x 128 (1024 items): 256 / 512 blocks 40 / 38 us
 static_assert(kSelBlocks <= kRedBlocks, "the workspace holds the partial sums");
 constexpr int kFlushItems = 4096;  // items whose sums fit a lane's and a wave's 32 bits (32 * 255 * 64 * 4096 < 2^32)
 
 struct SelState {
-  unsigned long long part[2][GC_MAX_VIEWS][kRedBlocks];   // of this and the previous round: [candidate][block]
+  unsigned long long part[2][kRedBlocks * GC_MAX_VIEWS];  // of this and the previous round: [block][candidate]
   unsigned long long chosen[GC_MAX_ANCHORS + 1];          // views chosen before round r
 };
 
 int sel_blocks(int64_t n_items) { return (int)(n_items < kSelBlocks ? n_items : kSelBlocks); }
 
-// wave_add for 64-bit sums.
-__device__ __forceinline__ unsigned long long wave_add64(unsigned long long v) {
-#define GC_ADD64(ctrl)                                                                                      \
-  v += (unsigned long long)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, ctrl, 0xf, 0xf, false) |    \
-       (unsigned long long)(uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), ctrl, 0xf, 0xf, false) << 32
-  GC_ADD64(kDppXor1);
-  GC_ADD64(kDppXor2);
-  GC_ADD64(kDppHalfMirror);
-  GC_ADD64(kDppMirror);
-#undef GC_ADD64
-  unsigned long long sum = 0ull;
-#pragma unroll
-  for (int r = 0; r < 64; r += 16)
-    sum += (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, r) |
-           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), r) << 32;
-  return sum;
-}
-
 // The sums over the blocks' partials of candidates 0 .. n - 1 to out (LDS);
-// every thread of the block calls it, and it ends on a barrier.  A wave takes
-// CPW candidates at a time (wave w: w, w + waves, ...), all loads together.
-template <int CPW>
-__device__ __forceinline__ void sum_partials(const unsigned long long (*part)[kRedBlocks], int n, int nblk,
+// every thread of the block (a multiple of 64, at least GC_MAX_VIEWS) calls it,
+// and it ends on a barrier.  A thread's stride is a multiple of n, so it adds
+// one candidate's partials from coalesced loads that depend on nothing.
+__device__ __forceinline__ void sum_partials(const unsigned long long* __restrict__ part, int n, int nblk,
                                              unsigned long long* out) {
-  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), lane = __lane_id();
-  const int waves = (int)blockDim.x / 64;
-  for (int u0 = wv; u0 < n; u0 += CPW * waves) {
-    unsigned long long acc[CPW] = {};
-    for (int i = lane; i < nblk; i += 64)
-#pragma unroll
-      for (int q = 0; q < CPW; ++q) acc[q] += part[min(u0 + q * waves, n - 1)][i];
-#pragma unroll
-    for (int q = 0; q < CPW; ++q) {
-      const unsigned long long sum = wave_add64(acc[q]);
-      if (lane == 0 && u0 + q * waves < n) out[u0 + q * waves] = sum;
-    }
+  const int t = (int)threadIdx.x, T = (int)blockDim.x / n * n;
+  if (t < n) out[t] = 0ull;
+  unsigned long long acc = 0ull;
+  if (t < T) {
+#pragma unroll 8
+    for (int i = t; i < n * nblk; i += T) acc += part[i];
   }
+  __syncthreads();
+  if (t < T) atomicAdd(&out[t % n], acc);
   __syncthreads();
 }
 
 // The views chosen before round r (r >= 1): those before round r - 1 and the
 // unchosen view with the largest gain of that round (ties: lower view).
-template <int CPW>
 __device__ __forceinline__ unsigned long long chosen_before(const SelState* st, int r, int N, int nblk,
                                                             unsigned long long* gain) {
   unsigned long long chosen = st->chosen[r - 1];
-  sum_partials<CPW>(st->part[(r - 1) & 1], N, nblk, gain);
+  sum_partials(st->part[(r - 1) & 1], N, nblk, gain);
   const int lane = __lane_id();
   const bool cand = lane < N && !((chosen >> lane) & 1ull);
   const unsigned long long g = cand ? gain[lane] : 0ull;
@@ -730,7 +720,7 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_round(const uint32_t* __restr
     }
   };
   if (blockIdx.x < n_items) load(blockIdx.x);   // in flight while the view of the last round is picked
-  const unsigned long long chosen = r == 0 ? forced : chosen_before<VPW>(st, r, N, nblk, gain);
+  const unsigned long long chosen = r == 0 ? forced : chosen_before(st, r, N, nblk, gain);
   if (blockIdx.x == 0 && threadIdx.x == 0) st->chosen[r] = chosen;
   uint32_t acc[VPW] = {};
   unsigned long long total[VPW] = {};
@@ -775,7 +765,7 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_round(const uint32_t* __restr
   for (int q = 0; q < VPW; ++q) {
     const int u = q * kSelWaves + wv;
     total[q] += wave_add(acc[q]);
-    if (u < N && lane == 0) st->part[r & 1][u][blockIdx.x] = total[q];
+    if (u < N && lane == 0) st->part[r & 1][blockIdx.x * N + u] = total[q];
   }
 }
 
@@ -828,7 +818,7 @@ __global__ __launch_bounds__(kSelBlock) void k_score_pass(const uint32_t* __rest
     __syncthreads();   // the next item's words overwrite these
   }
   // a wave's lanes hold its own sets' totals; the partials of set s sit with wave s % kSelWaves
-  if (lane < M && lane % kSelWaves == wv) st->part[0][lane][blockIdx.x] = mine;
+  if (lane < M && lane % kSelWaves == wv) st->part[0][blockIdx.x * M + lane] = mine;
 }
 
 // The result (block 0) after `rounds` rounds of k_sel_round or one pass of
@@ -842,10 +832,10 @@ __global__ __launch_bounds__(kRowBlock) void k_cov_final(const SelState* st, int
   if (blockIdx.x == 0) {
     __shared__ unsigned long long sum[kMaxSets];
     if constexpr (SCORE) {
-      sum_partials<8>(st->part[0], M, nblk, sum);
+      sum_partials(st->part[0], M, nblk, sum);
       if ((int)threadIdx.x < M) score[threadIdx.x] = sum[threadIdx.x];
     } else {
-      write_set(rounds ? chosen_before<8>(st, rounds, N, nblk, sum) : forced, out);
+      write_set(rounds ? chosen_before(st, rounds, N, nblk, sum) : forced, out);
     }
   }
   if constexpr (STATS) {
@@ -928,7 +918,7 @@ extern "C" int gc_coverage_init(const float* pos, int B, int N, int H, int W, ui
   if (rc) return rc;
   const int64_t n_tok = (int64_t)B * N * H * W;
   if (overlaps(stale, (size_t)n_tok, pos, (size_t)n_tok * 12)) return fail(GC_ERR_ALIAS, "gc_coverage_init: stale overlaps pos");
-  hipLaunchKernelGGL(k_cov_init, dim3((unsigned)((n_tok + kBlock - 1) / kBlock)), dim3(kBlock), 0, stream, pos, n_tok,
+  hipLaunchKernelGGL(k_cov_init, dim3((unsigned)((n_tok + 4 * kBlock - 1) / (4 * kBlock))), dim3(kBlock), 0, stream, pos, n_tok,
                      stale);
   return after_launch(stream, "gc_coverage_init");
 }

@@ -54,3 +54,20 @@ def test_update_select_score_many_views(gc, N, B, H, W, offset):
     left = buf.clone()
     left[offset:offset + n] = 0
     assert not left.any()   # nothing written around the staleness
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 1023, 1024, 4093])
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_initial_staleness(gc, n, offset):
+    """0 for foreground and 255 for background, whatever the count leaves for
+    the last thread and wherever the bytes start."""
+    rs = np.random.default_rng(n)
+    P = rs.standard_normal((1, 1, 1, n, 3)).astype(np.float32)
+    P[0, 0, 0, rs.random(n) < 0.5, 1] = np.nan
+    P[0, 0, 0, rs.random(n) < 0.1, 2] = -np.inf
+    buf = torch.full((n + 16,), 7, dtype=torch.uint8, device=DEV)
+    out = buf[offset:offset + n].view(1, 1, 1, n)
+    gc.gc_coverage_init(torch.from_numpy(P).to(DEV), out=out)
+    want = np.full(n + 16, 7, np.uint8)
+    want[offset:offset + n] = np.where(np.isfinite(P[0, 0, 0]).all(-1), 0, 255)
+    np.testing.assert_array_equal(buf.cpu().numpy(), want)
