@@ -10,14 +10,24 @@
 //
 // Small chunks: with larger ones fewer groups of 64 are partly filled, but a
 // dense block's chain of groups grows while its neighbours are empty (8 assets
-// x 12 views of 128 x 128, chunks of 128 / 256 / 512 / 1024 tokens: visibility
-// pairs 36 / 35 / 55 / 73 us, builder 18.7 / 21.6 / 34 / 43 us).
+// x 12 views of 128 x 128: visibility pairs with chunks of 256 / 512 / 1024
+// tokens 28 / 30 / 37 us, builder with 128 / 256 17.9 / 19.6 us).
 #pragma once
 
 #include "gc_common.h"
 #include "gc_geometry.h"
 
 namespace gc {
+
+// First chunk of the block (x, y): x rotated by three chunks per row y.  Views
+// have their foreground in the same places, and blocks are dealt to XCDs and
+// CUs round-robin: in plain order some CUs get the dense chunks of every view
+// and others the empty ones, where the chunks per view and the CUs have a
+// common factor (visibility pairs of 8 assets x 12 views of 128 x 128 32.3 us
+// in plain order, 28.0 rotated; 6 x 16 views 40.0 and 33.8; builder 18.7 and
+// 17.9; grids without such a factor, 75 x 101 or 160 x 160, the same within
+// 3 %; rotations by 1, 7 and 11 in between).
+__device__ __forceinline__ int rotated_chunk() { return (int)((blockIdx.x + blockIdx.y * 3u) % gridDim.x); }
 
 // A chunk of TOK tokens: one per thread of a block of TOK.
 template <int TOK> struct CompactLds {

@@ -24,8 +24,7 @@ namespace {
 constexpr int kBuildBlocksPerCU = 16;
 constexpr int kBuildBlocksPerCUStats = 4;
 // Tokens per chunk, and threads per block.  Groups of four lanes: 128 (8 assets
-// x 8 target views of 128 x 128 with 4 anchors 18.5 us; 64 20.0, 192 19.2, 256
-// 21.6).  With the counters, whose atomics grow with the blocks, 256 (21.6 us;
+// x 8 target views of 128 x 128 with 4 anchors 17.9 us; 256 19.6).  With the counters, whose atomics grow with the blocks, 256 (21.6 us;
 // 192 25.5, 128 28.4), as with groups of eight lanes (3 assets x 10 target
 // views of 75 x 101 with 6 anchors 12.0 us; 128 13.7, 64 15.4).
 constexpr int build_tok(int group, bool count) { return group == 4 && !count ? 128 : 256; }
@@ -56,9 +55,9 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return v;
 }
 
-// Bound by vector-ALU issue (12 of 18.5 us) and by the chain of a block's loads;
+// Bound by vector-ALU issue (12 of 17.9 us) and by the chain of a block's loads;
 // without the compaction a lane per (raster token, slot) took 24.6 us on 8
-// assets x 8 target views of 128 x 128 with 4 anchors, now 18.5 (34 -> 21.6 us
+// assets x 8 target views of 128 x 128 with 4 anchors, now 17.9 (34 -> 21.6 us
 // with the counters).
 //
 // A block compacts the foreground tokens of a chunk of one target view, writes
@@ -98,7 +97,7 @@ __global__ __launch_bounds__(build_tok(G, COUNT)) void k_build(BuildArgs g) {
   const int n_chunks = (HW + kTok - 1) / kTok;
   uint32_t c_pairs = 0, c_pix = 0, c_fg = 0;   // wave totals (uniform across the wave)
   uint32_t taps_lane = 0;                       // this lane's kept taps, summed over the wave at the end
-  for (int chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
+  for (int chunk = rotated_chunk(); chunk < n_chunks; chunk += gridDim.x) {
     const int p0 = chunk * kTok;
     int n_fg;
     const int rank = compact_foreground(view, HW, p0, list, &n_fg);   // its barriers also order the cameras

@@ -68,7 +68,7 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 
 constexpr int kCompactTok = 256;   // tokens per chunk, and threads per block
 constexpr int kCompactWaves = kCompactTok / 64;
-constexpr int kPairBatch = 2;   // anchors whose tap loads a wave keeps in flight together (1: 45 us, 2 and 3: 35, 4: 39)
+constexpr int kPairBatch = 2;   // anchors whose tap loads a wave keeps in flight together (before the rotation 1: 45 us, 2 and 3: 35, 4: 39)
 
 // One block per chunk of kCompactTok tokens of a view (grid: x = chunk,
 // y = b * N + v), for every anchor u: the chunk's foreground tokens are
@@ -76,8 +76,8 @@ constexpr int kPairBatch = 2;   // anchors whose tap loads a wave keeps in fligh
 // turn, each leaving one ballot per anchor, and the rows' bits are put
 // together from the ballots by the tokens' ranks.  The anchor is the same for
 // a whole wave, so its camera sits in scalar registers.
-// Bound by vector-ALU issue (25 of 35 us; two IEEE divisions and four tap
-// tests per pair).  8 assets x 12 views of 128 x 128: 78 -> 35 us against a
+// Bound by vector-ALU issue (23 of 28 us; two IEEE divisions and four tap
+// distances per pair).  8 assets x 12 views of 128 x 128: 78 -> 28 us against a
 // lane per raster token and anchor, which also formed the unused weights.
 __global__ __launch_bounds__(kCompactTok) void k_cov_pairs(const float* __restrict__ pos,
                                                            const gc_camera* __restrict__ cams,
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kCompactTok) void k_cov_pairs(const float* __restri
   const int bv = blockIdx.y;
   const int b = bv / N, v = bv - b * N;
   const int HW = H * W;
-  const int p0 = blockIdx.x * kCompactTok;
+  const int p0 = rotated_chunk() * kCompactTok;
   const int w0 = p0 / 32;
   int n_fg;
   const int rank = compact_foreground(pos + (int64_t)bv * HW * 3, HW, p0, s, &n_fg);

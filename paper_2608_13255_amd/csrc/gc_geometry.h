@@ -124,13 +124,26 @@ __device__ __forceinline__ void taps_in_tolerance(const float (&P)[3], const Anc
 }
 
 // Whether the anchor sees P: some tap is valid (the word of anchor_select is
-// non-zero exactly then).
+// non-zero exactly then).  A tap off the grid was read at the neighbouring
+// pixel on it, which is the footprint's other tap of that row or column unless
+// both are off, so with the footprint touching the grid the nearest of the
+// four distances decides (a NaN is never the nearest).
 __device__ __forceinline__ bool anchor_sees(const float (&P)[3], const AnchorProj& pj, const TapPos& tp, int H, int W,
                                             float tol2) {
-  bool valid[4];
+  if (__ballot(!finite_f(tol2))) {
+    bool valid[4];
+    float d2[4];
+    taps_in_tolerance(P, pj, tp, H, W, tol2, valid, d2);
+    return pj.ok & (valid[0] | valid[1] | valid[2] | valid[3]);
+  }
   float d2[4];
-  taps_in_tolerance(P, pj, tp, H, W, tol2, valid, d2);
-  return pj.ok & (valid[0] | valid[1] | valid[2] | valid[3]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float dx = tp.q[k][0] - P[0], dy = tp.q[k][1] - P[1], dz = tp.q[k][2] - P[2];
+    d2[k] = (dx * dx + dy * dy) + dz * dz;
+  }
+  const float nearest = __builtin_fminf(__builtin_fminf(d2[0], d2[1]), __builtin_fminf(d2[2], d2[3]));
+  return pj.ok & ((uint32_t)(pj.x0 + 1) <= (uint32_t)W) & ((uint32_t)(pj.y0 + 1) <= (uint32_t)H) & (nearest <= tol2);
 }
 
 // The per-tap tolerance test, the K nearest valid taps and their normalised
