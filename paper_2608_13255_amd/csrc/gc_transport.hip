@@ -20,10 +20,10 @@
 // from only its own assets' anchor views, which fit its L2; streaming blocks
 // over all rows follow in the hardware's round-robin order and skip the
 // visible tokens by their bit.  Data each thread touches once (its own
-// x0_prev and x_t, every output) is read and written with nontemporal hints;
-// the gathered anchor tiles, and an anchor row's own inputs that the gathers
-// also read (its new prediction, its x0_prev for UniPC), go through L2
-// normally.
+// x0_prev and x_t, the outputs) is read and written with nontemporal hints;
+// the gathered anchor tiles, an anchor row's own inputs that the gathers also
+// read (its new prediction, its x0_prev for UniPC), and UniPC's corrected
+// sample, which the next step reads, go through L2 normally.
 #include "gc_common.h"
 #include "gc_latent.h"
 

@@ -13,8 +13,8 @@ from conftest import listed_in_tile_order
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
-SHAPES = [(1, 1, 1), (3, 1, 700), (2, 700, 1), (5, 17, 33), (7, 31, 49), (1, 3, 4094), (1, 4094, 3), (9, 75, 101),
-          (64, 512, 512), (66, 511, 509)]
+SHAPES = [(1, 1, 1), (3, 1, 700), (2, 700, 1), (5, 17, 33), (7, 31, 49), (1, 3, 4094), (1, 4094, 3), (9, 75, 101)]
+LARGE = [(64, 512, 512), (66, 511, 509)]   # 16384 chunks and a few more
 
 
 @pytest.fixture(scope="module")
@@ -29,13 +29,11 @@ def check_bits(words, flags):
     assert not un[flags.size:].any()
 
 
-@pytest.mark.parametrize("n_views,H,W", SHAPES)
-@pytest.mark.parametrize("density", [0.0, 0.3, 1.0])
+@pytest.mark.parametrize("n_views,H,W,density", [(*s, d) for s in SHAPES for d in (0.0, 0.3, 1.0)] +
+                         [(*s, 0.3) for s in LARGE])
 def test_indexes_match_their_definition(gc, n_views, H, W, density):
     rs = np.random.default_rng(n_views * 7919 + H * 31 + W)
     n = n_views * H * W
-    if n > 1 << 20 and density != 0.3:
-        pytest.skip("the large counts once")
     a = 1 if n > 1 << 20 else int(rs.integers(1, 9))
     flags = rs.random(n) < density
     want = listed_in_tile_order(flags, H, W)
