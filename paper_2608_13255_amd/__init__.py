@@ -74,9 +74,10 @@ class Sampler:
         return _sampler_struct(self.kind, self.pred_out, self.T, self.beta_start, self.beta_end)
 
 
-@functools.lru_cache(maxsize=64)
+@functools.lru_cache(maxsize=64, typed=True)
 def _sampler_struct(kind, pred_out, T, beta_start, beta_end) -> _Sampler:
-    """The C form of a sampler's (immutable) parameters; nothing writes to it."""
+    """The C form of a sampler's (immutable) parameters; nothing writes to it.
+    Typed: T = 1000.0 is no int32 and stays refused beside T = 1000."""
     return _Sampler(kind, pred_out, T, 0, beta_start, beta_end)
 
 
