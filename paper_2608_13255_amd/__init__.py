@@ -12,7 +12,6 @@ library has not been built.
 from __future__ import annotations
 
 import ctypes
-import functools
 import os
 from dataclasses import dataclass
 from typing import Dict, List, Optional, Sequence, Tuple
@@ -71,14 +70,9 @@ class Sampler:
     beta_end: float = 0.02
 
     def c(self) -> _Sampler:
-        return _sampler_struct(self.kind, self.pred_out, self.T, self.beta_start, self.beta_end)
-
-
-@functools.lru_cache(maxsize=64, typed=True)
-def _sampler_struct(kind, pred_out, T, beta_start, beta_end) -> _Sampler:
-    """The C form of a sampler's (immutable) parameters; nothing writes to it.
-    Typed: T = 1000.0 is no int32 and stays refused beside T = 1000."""
-    return _Sampler(kind, pred_out, T, 0, beta_start, beta_end)
+        """The C form, made anew: the caller's own to write to, from what the
+        fields hold now."""
+        return _Sampler(self.kind, self.pred_out, self.T, 0, self.beta_start, self.beta_end)
 
 
 _LIB = None

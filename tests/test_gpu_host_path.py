@@ -1,7 +1,8 @@
 """The binding's short cuts on the way to a launch: the raw handle of torch's
 current stream follows the stream context of each thread, a tensor that is not
 a contiguous device tensor is refused as before, and a sampler's C form is not
-shared between samplers that differ."""
+shared, neither between samplers that differ nor with a caller that writes to
+one."""
 import threading
 
 import numpy as np
@@ -59,6 +60,9 @@ class FakeMap:
 def test_sampler_structs_are_their_own(gc):
     x0 = torch.randn((1, 4, 8, 8, 4), device=DEV)
     xt = torch.randn_like(x0)
-    outs = [gc.gc_sampler_reconstruct(xt, x0, gc.Sampler(beta_end=b), 600, 500)[0] for b in (0.02, 0.012, 0.02)]
+    outs = []
+    for b in (0.02, 0.012, 0.02):
+        outs.append(gc.gc_sampler_reconstruct(xt, x0, gc.Sampler(beta_end=b), 600, 500)[0])
+        gc.Sampler(beta_end=b).c().beta_end = 0.5   # a struct of this caller's own
     assert torch.equal(outs[0], outs[2]) and not torch.equal(outs[0], outs[1])
     assert np.isfinite(outs[1].cpu().numpy()).all()
