@@ -370,6 +370,8 @@ constexpr int kHistThreads = 1024;                // 4 lanes per pair word, 8 to
 constexpr int kHistBlocks = 256;                  // blocks of the token pass (more for huge inputs)
 constexpr int64_t kHistMaxWords = 1 << 16;        // words per block: 2^21 tokens * 255 < 2^32 per LDS bin
 
+constexpr int kWaitVm0 = 0x0f70;                  // s_waitcnt vmcnt(0), the other counters at their maxima
+
 struct HistState {
   unsigned long long H[kHistBins];
   unsigned int ticket;                            // blocks of the token pass that have added their bins
@@ -557,9 +559,14 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
   __syncthreads();
   for (int i = (int)threadIdx.x; i < nb; i += kHistThreads)
     if (h[i]) atomicAdd(&hs->H[i], (unsigned long long)h[i]);
-  // The last block to add its bins computes the result (no block waits).
-  // The barrier waits for this block's bin atomics; one acquire-release
-  // ticket per block orders them before the last block's reads of H.
+  // The last block to add its bins computes the result (no block waits).  A
+  // barrier waits for no memory operation and the ticket's release only for
+  // those of its own wave, so every wave lets its bin atomics complete before
+  // the barrier; the block's acquire-release ticket (whose release covers the
+  // XCD's L2 for all of them) then orders them before the last block's reads
+  // of H.  A release fence per wave instead, each writing back L2, takes the
+  // kernel from 18.7 to 39.8 us (8 x 12 views of 128 x 128).
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
   __syncthreads();
   if (threadIdx.x == 0)
     last = __hip_atomic_fetch_add(&hs->ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
