@@ -70,6 +70,30 @@ constexpr int kCompactTok = 256;   // tokens per chunk, and threads per block
 constexpr int kCompactWaves = kCompactTok / 64;
 constexpr int kPairBatch = 2;   // anchors whose tap loads a wave keeps in flight together (before the rotation 1: 45 us, 2 and 3: 35, 4: 39)
 
+// Ballots m[q] of the lanes whose token P (live: one to look at) anchor u0 + q
+// of asset b sees; u0 is wave-uniform, and an anchor past the last view repeats
+// the last one, for the caller to drop.
+__device__ __forceinline__ void pair_ballots(const float (&P)[3], bool live, const float* __restrict__ pos,
+                                             const gc_camera* __restrict__ cams, int b, int N, int u0, int H, int W,
+                                             float tol2, unsigned long long (&m)[kPairBatch]) {
+  AnchorProj pj[kPairBatch];
+  bool any = false;
+#pragma unroll
+  for (int q = 0; q < kPairBatch; ++q) {
+    pj[q] = anchor_project(P, wave_camera(cams + (int64_t)b * N + min(u0 + q, N - 1)), H, W);
+    any |= pj[q].ok;
+    m[q] = 0ull;
+  }
+  if (__ballot(any & live)) {
+    TapPos tp[kPairBatch];
+#pragma unroll
+    for (int q = 0; q < kPairBatch; ++q)
+      tp[q] = anchor_tap_positions(pj[q], pos + ((int64_t)b * N + min(u0 + q, N - 1)) * H * W * 3, H, W);
+#pragma unroll
+    for (int q = 0; q < kPairBatch; ++q) m[q] = __ballot(live & anchor_sees(P, pj[q], tp[q], H, W, tol2));
+  }
+}
+
 // One block per chunk of kCompactTok tokens of a view (grid: x = chunk,
 // y = b * N + v), for every anchor u: the chunk's foreground tokens are
 // compacted once, the waves take the (anchors, group of 64 of them) items in
@@ -113,22 +137,8 @@ __global__ __launch_bounds__(kCompactTok) void k_cov_pairs(const float* __restri
     const bool live = i < n_fg;
     const int j = live ? i : 0;
     const float P[3] = {s.q[0][j], s.q[1][j], s.q[2][j]};
-    AnchorProj pj[kPairBatch];
-    bool any = false;
-#pragma unroll
-    for (int q = 0; q < kPairBatch; ++q) {   // a view past the last repeats the last one and is dropped
-      pj[q] = anchor_project(P, wave_camera(cams + (int64_t)b * N + min(ub * kPairBatch + q, N - 1)), H, W);
-      any |= pj[q].ok;
-    }
-    unsigned long long m[kPairBatch] = {};
-    if (__ballot(any & live)) {
-      TapPos tp[kPairBatch];
-#pragma unroll
-      for (int q = 0; q < kPairBatch; ++q)
-        tp[q] = anchor_tap_positions(pj[q], pos + ((int64_t)b * N + min(ub * kPairBatch + q, N - 1)) * HW * 3, H, W);
-#pragma unroll
-      for (int q = 0; q < kPairBatch; ++q) m[q] = __ballot(live & anchor_sees(P, pj[q], tp[q], H, W, tol2));
-    }
+    unsigned long long m[kPairBatch];
+    pair_ballots(P, live, pos, cams, b, N, ub * kPairBatch, H, W, tol2, m);
 #pragma unroll
     for (int q = 0; q < kPairBatch; ++q)
       if (lane == 0 && ub * kPairBatch + q < N) seen[ub * kPairBatch + q][g] = m[q];
@@ -153,6 +163,46 @@ __global__ __launch_bounds__(kCompactTok) void k_cov_pairs(const float* __restri
     const int u = i / kWords, w = i - u * kWords;
     if (w0 + w < wpr) bits[(((int64_t)u * B + b) * N + v) * wpr + w0 + w] = words[u][w];
   }
+}
+
+// Small launches: a lane per raster token and kPairBatch anchors per block
+// (grid: x = chunk, y = b * N + v, z = batch of anchors).  Latency-bound there:
+// no barriers, and the anchors side by side instead of one after another in a
+// block.  One asset, per call: 6 views of 64 x 64 3.3 us (compacted 5.9), 12
+// of 32 x 32 3.2 (8.3), 64 of 16 x 16 5.2 (14.6).
+__global__ __launch_bounds__(kCompactTok) void k_cov_pairs_direct(const float* __restrict__ pos,
+                                                                  const gc_camera* __restrict__ cams,
+                                                                  const float* __restrict__ bbox, int B, int N, int H,
+                                                                  int W, int wpr, uint32_t* __restrict__ bits) {
+  const int bv = blockIdx.y;
+  const int b = bv / N, v = bv - b * N;
+  const int u0 = (int)blockIdx.z * kPairBatch;
+  const int HW = H * W;
+  const int p = (int)(blockIdx.x * kCompactTok + threadIdx.x);
+  const float* pp = pos + ((int64_t)bv * HW + min(p, HW - 1)) * 3;
+  const float P[3] = {pp[0], pp[1], pp[2]};
+  const bool live = p < HW && finite_f(P[0]) && finite_f(P[1]) && finite_f(P[2]);
+  unsigned long long m[kPairBatch];
+  pair_ballots(P, live, pos, cams, b, N, u0, H, W, bbox[(int64_t)b * 8 + 6], m);
+  const int lane = __lane_id();
+  const int w = p >> 5;   // a wave's tokens are two words of the row
+#pragma unroll
+  for (int q = 0; q < kPairBatch; ++q)
+    if ((lane & 31) == 0 && u0 + q < N && w < wpr)
+      bits[(((int64_t)(u0 + q) * B + b) * N + v) * wpr + w] = u0 + q == v ? 0u : (uint32_t)(m[q] >> (lane & 32));
+}
+
+// The direct launch by its blocks and the compacted one's (its grid without
+// the anchors).  Up to 2048 direct blocks everything is latency; above that
+// the direct launch pays for the background's lanes, and is ahead only while
+// the compacted one has too few blocks to hide their chains.  Direct /
+// compacted in us: 2 views of 512 x 512 (2048 and 2048 blocks) 4.7 / 5.3, 12 of
+// 128 x 128 (4608, 768) 8.5 / 9.9, 32 of 64 x 64 (8192, 512) 14.5 / 21.9, 8 x 4
+// of 128 x 128 (4096, 2048) 8.0 / 7.3, 2 x 12 of 128 x 128 (9216, 1536)
+// 14.3 / 11.9, 15 x 64 of 16 x 16 (30720, 960) 41.5 / 29.3, 64 of 64 x 64 (32768,
+// 1024) 49.7 / 53.8.
+bool pairs_direct(int64_t direct_blocks, int64_t compact_blocks) {
+  return direct_blocks <= 2048 || (direct_blocks <= 16384 && compact_blocks <= 1024);
 }
 
 // Four tokens per thread: three 16-byte loads (positions are 4-byte aligned)
@@ -913,8 +963,13 @@ extern "C" int gc_coverage_pairs(const float* pos, const gc_camera* cams, const 
   if (overlaps(pair_bits, nb, pos, (size_t)B * N * HW * 12) || overlaps(pair_bits, nb, cams, (size_t)B * N * sizeof(gc_camera)) ||
       overlaps(pair_bits, nb, bbox, (size_t)B * 32))
     return fail(GC_ERR_ALIAS, "gc_coverage_pairs: pair_bits overlaps an input");
-  const dim3 grid((unsigned)((HW + kCompactTok - 1) / kCompactTok), (unsigned)(B * N));
-  hipLaunchKernelGGL(k_cov_pairs, grid, dim3(kCompactTok), 0, stream, pos, cams, bbox, B, N, H, W, wpr, pair_bits);
+  const int64_t chunks = ((int64_t)HW + kCompactTok - 1) / kCompactTok, batches = (N + kPairBatch - 1) / kPairBatch;
+  if (pairs_direct(chunks * B * N * batches, chunks * B * N))
+    hipLaunchKernelGGL(k_cov_pairs_direct, dim3((unsigned)chunks, (unsigned)(B * N), (unsigned)batches),
+                       dim3(kCompactTok), 0, stream, pos, cams, bbox, B, N, H, W, wpr, pair_bits);
+  else
+    hipLaunchKernelGGL(k_cov_pairs, dim3((unsigned)chunks, (unsigned)(B * N)), dim3(kCompactTok), 0, stream, pos, cams,
+                       bbox, B, N, H, W, wpr, pair_bits);
   return after_launch(stream, "gc_coverage_pairs");
 }
 

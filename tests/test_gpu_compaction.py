@@ -1,8 +1,10 @@
-"""The kernels that evaluate the operator on compacted foreground tokens (the
-correspondence builder, with and without counters, and the visibility pairs),
-at the sizes where a chunk of 256 tokens or a group of 64 begins or ends:
-words, pair bits and counters bit-exact against the oracle, weights within a
-few float roundings of a quotient (1e-6).  Maps full of foreground, without
+"""The kernels that evaluate the operator (the correspondence builder, with
+and without counters, and the visibility pairs), at the sizes where a wave of
+64 tokens, a chunk of 128 or 256 or a group of 64 compacted foreground tokens
+begins or ends: words, pair bits and counters bit-exact against the oracle,
+weights within a few float roundings of a quotient (1e-6).  Single assets take
+the direct launches, a lane per raster token; the same views in large batches
+take those on compacted foreground tokens.  Maps full of foreground, without
 any, with one token and with random holes; NaN and infinite positions as
 background; pinhole and orthographic cameras in one rig; anchor counts on both
 sides of the four- and eight-lane groups; a squared tolerance that overflowed
@@ -47,6 +49,31 @@ def problem(seed, N, H, W, fill):
     return rs, P, cams
 
 
+def device_box(bb):
+    full = np.zeros((bb.shape[0], 8), np.float32)
+    full[:, :bb.shape[1]] = bb
+    return torch.from_numpy(full).to(DEV)
+
+
+def check_pairs(gc, P, cams, bb):
+    B, N, H, W = P.shape[:4]
+    pb = gc.gc_coverage_pairs(torch.from_numpy(P).to(DEV), gc.camera_tensor(cams, DEV), device_box(bb),
+                              out=torch.full((N, B, N, (H * W + 31) // 32), -1, dtype=torch.int32, device=DEV))
+    un = np.unpackbits(pb.cpu().numpy().view(np.uint8), axis=-1, bitorder="little").reshape(N, B, N, -1)
+    assert not un[..., H * W:].any()
+    np.testing.assert_array_equal(un[..., :H * W].reshape(N, B, N, H, W), oracle.coverage_pairs(P, cams, 4, bb))
+
+
+def batch(seed, B, N, H, W, fill):
+    """B assets with the views of one and holes of their own, the last without any foreground."""
+    rs, P, cams = problem(seed, N, H, W, fill)
+    P = np.repeat(P, B, axis=0)
+    if fill == "holes":
+        P[rs.random(P.shape[:-1]) < 0.3] = np.nan
+    P[-1] = np.nan
+    return rs, P, {k: np.repeat(v, B, axis=0) for k, v in cams.items()}
+
+
 @pytest.mark.parametrize("N,H,W,a,K,fill", [
     (3, 1, 1, 1, 4, "all"), (3, 1, 63, 2, 4, "all"), (4, 8, 8, 3, 1, "holes"), (4, 5, 13, 4, 4, "all"),
     (5, 15, 17, 4, 4, "holes"), (5, 16, 16, 4, 2, "all"), (6, 257, 1, 5, 4, "all"), (6, 16, 20, 5, 3, "holes"),
@@ -60,9 +87,7 @@ def test_builder_and_pairs_match_oracle(gc, N, H, W, a, K, fill, overflow):
     anchors = sorted(rs.choice(N, a, replace=False).tolist())
     corr_o, wts_o, nvis_o = oracle.build(P, cams, anchors, K, bb)
     Pd, cams_d = torch.from_numpy(P).to(DEV), gc.camera_tensor(cams, DEV)
-    full = np.zeros((1, 8), np.float32)
-    full[:, :bb.shape[1]] = bb
-    bbd = torch.from_numpy(full).to(DEV)
+    bbd = device_box(bb)
     for counted in (False, True):
         stats = torch.full((1, 4), 77, dtype=torch.int32, device=DEV) if counted else None
         corr = torch.full((1, N - a, H, W, a), -1, dtype=torch.int32, device=DEV)
@@ -76,8 +101,19 @@ def test_builder_and_pairs_match_oracle(gc, N, H, W, a, K, fill, overflow):
                     int(np.isfinite(P[:, targets]).all(-1).sum()),
                     int(sum(((corr_o >> (24 + k)) & 1).sum() for k in range(4)))]
             assert stats.cpu().numpy()[0].tolist() == want
-    pb = gc.gc_coverage_pairs(Pd, cams_d, bbd).cpu().numpy().view(np.uint32)
-    un = np.unpackbits(np.ascontiguousarray(pb).view(np.uint8), axis=-1, bitorder="little")
-    un = un.reshape(N, 1, N, -1)
-    assert not un[..., H * W:].any()
-    np.testing.assert_array_equal(un[..., :H * W].reshape(N, 1, N, H, W), oracle.coverage_pairs(P, cams, 4, bb))
+    check_pairs(gc, P, cams, bb)
+
+
+@pytest.mark.parametrize("overflow", [False, True])
+@pytest.mark.parametrize("B,N,H,W,fill", [
+    # 1024 and 1026 compacted blocks, more than 2048 direct ones
+    (256, 4, 1, 63, "all"), (171, 6, 8, 8, "all"), (342, 3, 16, 16, "holes"), (129, 5, 257, 1, "all"),
+    (114, 9, 15, 17, "holes"), (65, 8, 16, 20, "one"), (65, 8, 23, 31, "holes"), (55, 13, 33, 32, "all"),
+    # 16384 direct blocks of few compacted ones, and some more
+    (64, 16, 3, 11, "holes"), (8, 64, 13, 17, "holes"), (9, 64, 16, 16, "all"), (15, 63, 7, 9, "all")])
+def test_pairs_of_batches_match_oracle(gc, B, N, H, W, fill, overflow):
+    _, P, cams = batch(11 + N * H + W, B, N, H, W, fill)
+    bb = oracle.bbox(P, 0.05).copy()
+    if overflow:
+        bb[::2, 6] = np.inf
+    check_pairs(gc, P, cams, bb)
