@@ -23,11 +23,27 @@ namespace {
 // blocks; one that does not uses enough blocks to hide its load latency.
 constexpr int kBuildBlocksPerCU = 16;
 constexpr int kBuildBlocksPerCUStats = 4;
-// Tokens per chunk, and threads per block.  Groups of four lanes: 128 (8 assets
-// x 8 target views of 128 x 128 with 4 anchors 17.9 us; 256 19.6).  With the counters, whose atomics grow with the blocks, 256 (21.6 us;
-// 192 25.5, 128 28.4), as with groups of eight lanes (3 assets x 10 target
+// Tokens per chunk of a view.  Compacted chunks, a token per thread: groups of
+// four lanes 128 (8 assets x 8 target views of 128 x 128 with 4 anchors 17.9 us;
+// 256 19.6); with the counters, whose atomics grow with the blocks, 256 (21.6
+// us; 192 25.5, 128 28.4), as with groups of eight lanes (3 assets x 10 target
 // views of 75 x 101 with 6 anchors 12.0 us; 128 13.7, 64 15.4).
-constexpr int build_tok(int group, bool count) { return group == 4 && !count ? 128 : 256; }
+constexpr int build_threads(int group, bool count, bool compact) { return compact && group == 4 && !count ? 128 : 256; }
+constexpr int build_tok(int group, bool count, bool compact) {
+  return build_threads(group, count, compact) / (compact ? 1 : group);
+}
+
+// Target tokens up to which a build takes the direct launch.  Direct /
+// compacted in us, one asset unless said: 5 target views of 64 x 64, 1 anchor
+// 3.8 / 7.1; 4 of 64 x 64, 8 anchors 4.1 / 11.3; 8 assets x 8 of 128 x 128 (2^20
+// tokens), 4 anchors 20.5 / 17.9; around the lines: 4 x 8 of 128 x 128 (2^19), 4
+// anchors 12.3 / 13.4; 4 x 10 (655,360), 2 anchors 13.0 / 12.7; 8 x 6 (786,432), 6
+// anchors 25.6 / 25.9; 8 x 7 (917,504), 5 anchors 28.2 / 26.5.  With the counters,
+// whose few long blocks hide less of the chain: 12 of 64 x 64 (49,152), 4
+// anchors 9.4 / 9.7; 2 x 8 of 64 x 64 (65,536) 10.7 / 9.8.
+bool build_direct(int64_t tokens, int a, bool count) {
+  return tokens <= (count ? 3 << 14 : a <= 4 ? 1 << 19 : 3 << 18);
+}
 
 struct BuildArgs {
   const float* pos;
@@ -55,28 +71,95 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return v;
 }
 
-// Bound by vector-ALU issue (12 of 17.9 us) and by the chain of a block's loads;
-// without the compaction a lane per (raster token, slot) took 24.6 us on 8
-// assets x 8 target views of 128 x 128 with 4 anchors, now 17.9 (34 -> 21.6 us
-// with the counters).
-//
-// A block compacts the foreground tokens of a chunk of one target view, writes
-// the other tokens' zero words, and then gives each (compacted token, anchor
-// slot) a lane: a group of G = 4 or 8 adjacent lanes serves one token (lanes
-// with slot >= a idle).  Each lane projects the token into its own anchor,
-// tests the four footprint taps, keeps the K nearest and forms that anchor's
-// normalised area weights; the number of anchors that see the token (n_vis)
-// is a ballot over the lane group.  Words and weights of one token are
-// adjacent, so a group writes them coalesced.  The block's anchor cameras are
-// staged in LDS.
-// grid: y = b * NT + target slot; x = blocks that stride over the view's
-// chunks.  A block counts its visible pairs / tokens / foreground tokens /
-// taps over all its chunks and adds them to the asset's counters once: few
-// blocks per asset keep the same-address atomics from serialising.
+// A block's visible pairs, visible tokens, foreground tokens and kept taps.
+struct BuildCounts {
+  uint32_t pairs = 0, pix = 0, fg = 0;   // wave totals (uniform across the wave)
+  uint32_t taps_lane = 0;                // this lane's kept taps, summed over the wave at the end
+};
+
+// One (token, anchor slot s) per lane, a token's slots in G adjacent lanes:
+// projection into the slot's anchor, the four footprint taps' tests, the K
+// nearest and their normalised area weights; the number of anchors that see
+// the token (n_vis) is a ballot over the lane group.  Words and weights of one
+// token are adjacent, so a group writes them coalesced.  eval: the token is
+// foreground and the slot an anchor's; store: the slot's word is written;
+// row: the token's row of the operator.  Every lane of the wave calls it.
 template <int G, bool COUNT>
-__global__ __launch_bounds__(build_tok(G, COUNT)) void k_build(BuildArgs g) {
-  constexpr int kTok = build_tok(G, COUNT);
-  __shared__ CompactLds<kTok> list;
+__device__ __forceinline__ void build_pair(const BuildArgs& g, const float (&P)[3], const gc_camera& cam,
+                                           const float* __restrict__ src, float tol2, int s, bool eval, bool store,
+                                           int64_t row, BuildCounts& cnt) {
+  AnchorProj pj = anchor_project(P, cam, g.H, g.W);
+  pj.ok &= eval;
+  AnchorTaps at;
+  at.word = 0;
+  at.mask = 0;
+  if (__ballot(pj.ok)) {
+    const TapPos tp = anchor_tap_positions(pj, src, g.H, g.W);
+    at = anchor_select(P, pj, tp, g.H, g.W, g.K, tol2);
+  }
+  // n_vis: anchors of this token that see it -- a ballot over the lane group
+  const unsigned long long seen = __ballot(at.word != 0);
+  const int n_vis = __popcll((seen >> (__lane_id() & ~(G - 1))) & ((1ull << G) - 1));
+  if (store) g.corr[row * g.a + s] = at.word;
+  // weights only for pairs the anchor sees: the transport reads a pair's
+  // weights only when its word is non-zero (most pairs' words are zero)
+  if (at.word != 0) {
+    float out[4] = {0.f, 0.f, 0.f, 0.f};
+    const float inv = (float)n_vis;
+    if (__ballot((n_vis & (n_vis - 1)) != 0)) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) at.wk[k] = at.wk[k] / inv;
+    } else {   // dividing by a power of two is multiplying by its exact reciprocal
+      const float rcp = __builtin_ldexpf(1.0f, -__builtin_ctz((unsigned)n_vis));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) at.wk[k] = at.wk[k] * rcp;
+    }
+#pragma unroll
+    for (int k = 3; k >= 0; --k) {   // the kept taps in ascending order, zeros behind them
+      const bool keep = at.mask & (1 << k);
+      const float w = at.wk[k];
+      out[3] = keep ? out[2] : out[3];
+      out[2] = keep ? out[1] : out[2];
+      out[1] = keep ? out[0] : out[1];
+      out[0] = keep ? w : out[0];
+    }
+    float* ww = g.weights + (row * g.a + s) * g.K;
+    if (g.K == 4) {   // 16-byte aligned: the weights base is, and each (token, slot) row is 16 bytes
+      *reinterpret_cast<float4*>(ww) = make_float4(out[0], out[1], out[2], out[3]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (q < g.K) ww[q] = out[q];
+    }
+  }
+  if (COUNT) {
+    cnt.pairs += (uint32_t)__popcll(seen);
+    cnt.pix += wave_count(s == 0 && n_vis > 0);
+    cnt.taps_lane += (uint32_t)__popc(at.mask);
+  }
+}
+
+// grid: y = b * NT + target slot; x = blocks that stride over the view's
+// chunks.  The block's anchor cameras are staged in LDS.  A block counts its
+// visible pairs / tokens / foreground tokens / taps over all its chunks and
+// adds them to the asset's counters once: few blocks per asset keep the
+// same-address atomics from serialising.
+//
+// COMPACT: a block compacts the foreground tokens of a chunk of one target
+// view, writes the other tokens' zero words, and then gives each (compacted
+// token, anchor slot) a lane: a group of G = 4 or 8 adjacent lanes serves one
+// token (lanes with slot >= a idle).  Bound by vector-ALU issue (12 of 17.9 us)
+// and by the chain of a block's loads: 8 assets x 8 target views of 128 x 128
+// with 4 anchors 17.9 us, 21.5 with the counters, against 20.5 and 30.6
+// without the compaction.
+// Otherwise: a lane per (raster token, slot), for small launches, which last
+// about as long as one block's chain: one group of tokens here, up to G of
+// them, one after another, in a compacted chunk.
+template <int G, bool COUNT, bool COMPACT>
+__global__ __launch_bounds__(build_threads(G, COUNT, COMPACT)) void k_build(BuildArgs g) {
+  constexpr int kThreads = build_threads(G, COUNT, COMPACT);
+  constexpr int kTok = build_tok(G, COUNT, COMPACT);
+  __shared__ CompactLds<COMPACT ? kTok : 64> list;
   __shared__ gc_camera cam_lds[GC_MAX_ANCHORS];
   __shared__ int32_t view_lds[GC_MAX_ANCHORS];   // a lane's own slot: from LDS, not a per-lane kernel-argument load
   const int HW = g.H * g.W;
@@ -90,106 +173,65 @@ __global__ __launch_bounds__(build_tok(G, COUNT)) void k_build(BuildArgs g) {
     cam_lds[threadIdx.x] = g.cams[(int64_t)b * g.N + g.anchor_view[threadIdx.x]];
   }
   const float tol2 = g.bbox[(int64_t)b * 8 + 6];
-  const int lane = __lane_id();
   const int s = (int)threadIdx.x & (G - 1);      // anchor slot of this lane
   const int sc = s < g.a ? s : 0;
-  const int gbase = lane & ~(G - 1);
   const int n_chunks = (HW + kTok - 1) / kTok;
-  uint32_t c_pairs = 0, c_pix = 0, c_fg = 0;   // wave totals (uniform across the wave)
-  uint32_t taps_lane = 0;                       // this lane's kept taps, summed over the wave at the end
-  for (int chunk = rotated_chunk(); chunk < n_chunks; chunk += gridDim.x) {
-    const int p0 = chunk * kTok;
-    int n_fg;
-    const int rank = compact_foreground(view, HW, p0, list, &n_fg);   // its barriers also order the cameras
-    const int p = p0 + (int)threadIdx.x;
-    if (rank < 0 && p < HW) {   // a background token: no anchor sees it
-      int32_t* cw = g.corr + (row0 + p) * g.a;
-      if (G == 4 && g.a == 4) {
-        *reinterpret_cast<int4*>(cw) = make_int4(0, 0, 0, 0);
-      } else {
-        for (int q = 0; q < g.a; ++q) cw[q] = 0;
-      }
-    }
-    if (COUNT && threadIdx.x / 64 == 0) c_fg += (uint32_t)n_fg;
-    for (int i0 = 0; i0 < n_fg; i0 += kTok / G) {
-      const int i = i0 + (int)threadIdx.x / G;
-      const bool live = i < n_fg && s < g.a;
-      const int ic = i < n_fg ? i : 0;
-      const float P[3] = {list.q[0][ic], list.q[1][ic], list.q[2][ic]};
-      AnchorProj pj = anchor_project(P, cam_lds[sc], g.H, g.W);
-      pj.ok &= live;
-      AnchorTaps at;
-      at.word = 0;
-      at.mask = 0;
-      if (__ballot(pj.ok)) {
-        const TapPos tp = anchor_tap_positions(pj, g.pos + ((int64_t)b * g.N + view_lds[sc]) * HW * 3, g.H, g.W);
-        at = anchor_select(P, pj, tp, g.H, g.W, g.K, tol2);
-      }
-      // n_vis: anchors of this token that see it -- a ballot over the lane group
-      const unsigned long long seen = __ballot(at.word != 0);
-      const int n_vis = __popcll((seen >> gbase) & ((1ull << G) - 1));
-      if (live) {
-        const int64_t row = row0 + p0 + list.at[ic];
-        g.corr[row * g.a + s] = at.word;
-        // weights only for pairs the anchor sees: the transport reads a pair's
-        // weights only when its word is non-zero (most pairs' words are zero)
-        if (at.word != 0) {
-          float out[4] = {0.f, 0.f, 0.f, 0.f};
-          const float inv = (float)n_vis;
-          if (__ballot((n_vis & (n_vis - 1)) != 0)) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) at.wk[k] = at.wk[k] / inv;
-          } else {   // dividing by a power of two is multiplying by its exact reciprocal
-            const float rcp = __builtin_ldexpf(1.0f, -__builtin_ctz((unsigned)n_vis));
-#pragma unroll
-            for (int k = 0; k < 4; ++k) at.wk[k] = at.wk[k] * rcp;
-          }
-#pragma unroll
-          for (int k = 3; k >= 0; --k) {   // the kept taps in ascending order, zeros behind them
-            const bool keep = at.mask & (1 << k);
-            const float w = at.wk[k];
-            out[3] = keep ? out[2] : out[3];
-            out[2] = keep ? out[1] : out[2];
-            out[1] = keep ? out[0] : out[1];
-            out[0] = keep ? w : out[0];
-          }
-          float* ww = g.weights + (row * g.a + s) * g.K;
-          if (g.K == 4) {   // 16-byte aligned: the weights base is, and each (token, slot) row is 16 bytes
-            *reinterpret_cast<float4*>(ww) = make_float4(out[0], out[1], out[2], out[3]);
-          } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (q < g.K) ww[q] = out[q];
-          }
+  BuildCounts cnt;
+  if constexpr (COMPACT) {
+    for (int chunk = rotated_chunk(); chunk < n_chunks; chunk += gridDim.x) {
+      const int p0 = chunk * kTok;
+      int n_fg;
+      const int rank = compact_foreground(view, HW, p0, list, &n_fg);   // its barriers also order the cameras
+      const int p = p0 + (int)threadIdx.x;
+      if (rank < 0 && p < HW) {   // a background token: no anchor sees it
+        int32_t* cw = g.corr + (row0 + p) * g.a;
+        if (G == 4 && g.a == 4) {
+          *reinterpret_cast<int4*>(cw) = make_int4(0, 0, 0, 0);
+        } else {
+          for (int q = 0; q < g.a; ++q) cw[q] = 0;
         }
       }
-      if (COUNT) {
-        const bool lead = s == 0 && i < n_fg;
-        c_pairs += (uint32_t)__popcll(seen);
-        c_pix += wave_count(lead && n_vis > 0);
-        taps_lane += (uint32_t)__popc(at.mask);
+      if (COUNT && threadIdx.x / 64 == 0) cnt.fg += (uint32_t)n_fg;
+      for (int i0 = 0; i0 < n_fg; i0 += kThreads / G) {
+        const int i = i0 + (int)threadIdx.x / G;
+        const bool live = i < n_fg && s < g.a;
+        const int ic = i < n_fg ? i : 0;
+        const float P[3] = {list.q[0][ic], list.q[1][ic], list.q[2][ic]};
+        build_pair<G, COUNT>(g, P, cam_lds[sc], g.pos + ((int64_t)b * g.N + view_lds[sc]) * HW * 3, tol2, s, live, live,
+                             row0 + p0 + list.at[ic], cnt);
       }
+      __syncthreads();   // the next chunk's compaction overwrites the list
     }
-    __syncthreads();   // the next chunk's compaction overwrites the list
+  } else {
+    __syncthreads();
+    for (int chunk = blockIdx.x; chunk < n_chunks; chunk += gridDim.x) {
+      const int p = chunk * kTok + (int)threadIdx.x / G;
+      const float* pp = view + (int64_t)min(p, HW - 1) * 3;
+      const float P[3] = {pp[0], pp[1], pp[2]};
+      const bool fg = p < HW && finite_f(P[0]) && finite_f(P[1]) && finite_f(P[2]);
+      if (COUNT) cnt.fg += wave_count(s == 0 && fg);
+      build_pair<G, COUNT>(g, P, cam_lds[sc], g.pos + ((int64_t)b * g.N + view_lds[sc]) * HW * 3, tol2, s,
+                           fg && s < g.a, p < HW && s < g.a, row0 + p, cnt);
+    }
   }
 
   if constexpr (COUNT) {
     // blocks never straddle assets (grid y is per asset and target): the
     // block sums its waves' totals in LDS, one thread per counter adds them
     // to the asset's counters
-    __shared__ uint32_t part[kTok / 64][4];
-    const uint32_t c_taps = wave_sum(taps_lane);
+    __shared__ uint32_t part[kThreads / 64][4];
+    const uint32_t c_taps = wave_sum(cnt.taps_lane);
     const int wv = (int)threadIdx.x / 64;
-    if (lane == 0) {
-      part[wv][0] = c_pairs;
-      part[wv][1] = c_pix;
-      part[wv][2] = c_fg;
+    if (__lane_id() == 0) {
+      part[wv][0] = cnt.pairs;
+      part[wv][1] = cnt.pix;
+      part[wv][2] = cnt.fg;
       part[wv][3] = c_taps;
     }
     __syncthreads();
     if (threadIdx.x < 4) {
       uint32_t sum = 0;
-      for (int w = 0; w < kTok / 64; ++w) sum += part[w][threadIdx.x];
+      for (int w = 0; w < kThreads / 64; ++w) sum += part[w][threadIdx.x];
       if (sum) atomicAdd(g.stats + (int64_t)b * 4 + threadIdx.x, sum);
     }
   }
@@ -249,20 +291,27 @@ extern "C" int gc_build_correspondence(const float* pos, const gc_camera* cams, 
   if (stats) hipLaunchKernelGGL(k_zero_u32, dim3((4 * B + 255) / 256), dim3(256), 0, stream, stats, 4 * B);
   if (NT > 0) {
     // x-blocks per (asset, target), from the launch size above
-#define GC_BUILD(G_, COUNT_)                                                                                  \
+#define GC_BUILD(G_, COUNT_, COMPACT_)                                                                        \
   do {                                                                                                        \
-    constexpr int tok = build_tok(G_, COUNT_);                                                                \
+    constexpr int tok = build_tok(G_, COUNT_, COMPACT_);                                                      \
     const int64_t chunks = ((int64_t)HW + tok - 1) / tok;                                                     \
     const int64_t per_cu = COUNT_ ? kBuildBlocksPerCUStats : kBuildBlocksPerCU;                               \
     int64_t bx = (per_cu * 256 + (int64_t)B * NT - 1) / ((int64_t)B * NT);                                    \
     if (bx > chunks) bx = chunks;                                                                             \
-    hipLaunchKernelGGL((k_build<G_, COUNT_>), dim3((unsigned)bx, (unsigned)(B * NT)), dim3(tok), 0, stream, g); \
+    hipLaunchKernelGGL((k_build<G_, COUNT_, COMPACT_>), dim3((unsigned)bx, (unsigned)(B * NT)),               \
+                       dim3(build_threads(G_, COUNT_, COMPACT_)), 0, stream, g);                              \
   } while (0)
-    if (a <= 4) {
-      if (stats) GC_BUILD(4, true); else GC_BUILD(4, false);
-    } else {
-      if (stats) GC_BUILD(8, true); else GC_BUILD(8, false);
-    }
+#define GC_BUILD_G(G_)                                                              \
+  do {                                                                              \
+    if (stats) {                                                                    \
+      if (direct) GC_BUILD(G_, true, false); else GC_BUILD(G_, true, true);         \
+    } else {                                                                        \
+      if (direct) GC_BUILD(G_, false, false); else GC_BUILD(G_, false, true);       \
+    }                                                                               \
+  } while (0)
+    const bool direct = build_direct((int64_t)B * NT * (int64_t)HW, a, stats != nullptr);
+    if (a <= 4) GC_BUILD_G(4); else GC_BUILD_G(8);
+#undef GC_BUILD_G
 #undef GC_BUILD
   }
   return after_launch(stream, "gc_build_correspondence");

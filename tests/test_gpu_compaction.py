@@ -55,6 +55,27 @@ def device_box(bb):
     return torch.from_numpy(full).to(DEV)
 
 
+def check_builder(gc, P, cams, bb, anchors, K):
+    B, N, H, W = P.shape[:4]
+    a = len(anchors)
+    corr_o, wts_o, nvis_o = oracle.build(P, cams, anchors, K, bb)
+    Pd, cams_d, bbd = torch.from_numpy(P).to(DEV), gc.camera_tensor(cams, DEV), device_box(bb)
+    for counted in (False, True):
+        stats = torch.full((B, 4), 77, dtype=torch.int32, device=DEV) if counted else None
+        corr = torch.full((B, N - a, H, W, a), -1, dtype=torch.int32, device=DEV)
+        wts = torch.zeros((B, N - a, H, W, a, K), dtype=torch.float32, device=DEV)
+        gc.gc_build_correspondence(Pd, cams_d, anchors, K, bbd, corr=corr, weights=wts, stats=stats)
+        np.testing.assert_array_equal(corr.cpu().numpy(), corr_o)
+        assert np.abs(visible_weights(corr, wts) - wts_o).max(initial=0.0) <= 1e-6
+        if counted:
+            targets = [v for v in range(N) if v not in anchors]
+            each = tuple(range(1, 5))
+            taps = sum(((corr_o >> (24 + k)) & 1).sum(axis=each) for k in range(4))
+            want = np.stack([(corr_o != 0).sum(axis=each), (nvis_o > 0).sum(axis=each[:-1]),
+                             np.isfinite(P[:, targets]).all(-1).sum(axis=each[:-1]), taps], axis=1)
+            np.testing.assert_array_equal(stats.cpu().numpy(), want)
+
+
 def check_pairs(gc, P, cams, bb):
     B, N, H, W = P.shape[:4]
     pb = gc.gc_coverage_pairs(torch.from_numpy(P).to(DEV), gc.camera_tensor(cams, DEV), device_box(bb),
@@ -85,22 +106,7 @@ def test_builder_and_pairs_match_oracle(gc, N, H, W, a, K, fill, overflow):
     if overflow:
         bb[:, 6] = np.inf
     anchors = sorted(rs.choice(N, a, replace=False).tolist())
-    corr_o, wts_o, nvis_o = oracle.build(P, cams, anchors, K, bb)
-    Pd, cams_d = torch.from_numpy(P).to(DEV), gc.camera_tensor(cams, DEV)
-    bbd = device_box(bb)
-    for counted in (False, True):
-        stats = torch.full((1, 4), 77, dtype=torch.int32, device=DEV) if counted else None
-        corr = torch.full((1, N - a, H, W, a), -1, dtype=torch.int32, device=DEV)
-        wts = torch.zeros((1, N - a, H, W, a, K), dtype=torch.float32, device=DEV)
-        gc.gc_build_correspondence(Pd, cams_d, anchors, K, bbd, corr=corr, weights=wts, stats=stats)
-        np.testing.assert_array_equal(corr.cpu().numpy(), corr_o)
-        assert np.abs(visible_weights(corr, wts) - wts_o).max(initial=0.0) <= 1e-6
-        if counted:
-            targets = [v for v in range(N) if v not in anchors]
-            want = [int((corr_o != 0).sum()), int((nvis_o > 0).sum()),
-                    int(np.isfinite(P[:, targets]).all(-1).sum()),
-                    int(sum(((corr_o >> (24 + k)) & 1).sum() for k in range(4)))]
-            assert stats.cpu().numpy()[0].tolist() == want
+    check_builder(gc, P, cams, bb, anchors, K)
     check_pairs(gc, P, cams, bb)
 
 
@@ -117,3 +123,19 @@ def test_pairs_of_batches_match_oracle(gc, B, N, H, W, fill, overflow):
     if overflow:
         bb[::2, 6] = np.inf
     check_pairs(gc, P, cams, bb)
+
+
+# target tokens up to and above each launch's line: 49,152 with the counters,
+# 524,288 (a <= 4) and 786,432 without
+@pytest.mark.parametrize("overflow", [False, True])
+@pytest.mark.parametrize("B,N,H,W,a,K,fill", [
+    (2048, 5, 8, 8, 1, 4, "all"), (2081, 5, 1, 63, 1, 1, "holes"), (683, 8, 8, 16, 2, 4, "all"),
+    (241, 12, 257, 1, 3, 2, "holes"), (256, 12, 16, 16, 4, 4, "all"), (197, 12, 19, 19, 4, 3, "holes"),
+    (64, 9, 8, 24, 5, 4, "holes"), (66, 9, 11, 17, 5, 4, "all"), (400, 14, 1, 257, 6, 4, "holes"),
+    (193, 24, 16, 16, 8, 2, "all"), (120, 32, 17, 16, 8, 4, "one")])
+def test_builds_of_batches_match_oracle(gc, B, N, H, W, a, K, fill, overflow):
+    rs, P, cams = batch(13 + N * H + W, B, N, H, W, fill)
+    bb = oracle.bbox(P, 0.05).copy()
+    if overflow:
+        bb[::2, 6] = np.inf
+    check_builder(gc, P, cams, bb, sorted(rs.choice(N, a, replace=False).tolist()), K)
