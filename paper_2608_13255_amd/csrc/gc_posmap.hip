@@ -159,6 +159,78 @@ __global__ __launch_bounds__(kBlock) void k_downsample_staged(const float* __res
   }
 }
 
+// Vector variant for f = 4 and 8 and small inputs: one thread per latent
+// pixel, each of its F render rows read as 3F/4 aligned 16-byte vectors (the
+// pixel's segment of a render row is 3F contiguous floats at a multiple of 48
+// bytes), kRows rows in flight per step.  The strided vectors of one wave tile
+// a contiguous run of the render row, so L2 serves the lines neighbouring
+// lanes share (plain loads: a nontemporal hint makes those lines miss); without
+// the staging's LDS round trip per step each thread folds its samples in the
+// same row-major order as the direct kernel.
+template <int F>
+__global__ __launch_bounds__(kBlock) void k_downsample_vec(const float* __restrict__ hi, int64_t n_pix, int Hr,
+                                                           int Wr, int H, int W, float* __restrict__ lo) {
+  constexpr int kRow4 = 3 * F / 4;          // vectors per render-row segment
+  constexpr int kRows = 4;                  // rows loaded together
+  static_assert(F % 4 == 0, "F must be a multiple of 4");
+  const int64_t gid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (gid >= n_pix) return;
+  const int i = (int)(gid % W);
+  const int64_t mj = gid / W;
+  const int j = (int)(mj % H);
+  const int64_t m = mj / H;
+  const f32x4* src = reinterpret_cast<const f32x4*>(hi + ((m * Hr + (int64_t)j * F) * Wr + (int64_t)i * F) * 3);
+  const int64_t rs = (int64_t)Wr * 3 / 4;   // vectors per render row
+  int n_fg = 0;
+  double sx = 0.0, sy = 0.0, sz = 0.0;
+  for (int dy0 = 0; dy0 < F; dy0 += kRows) {
+    float buf[kRows][3 * F];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+#pragma unroll
+      for (int c = 0; c < kRow4; ++c) {
+        const f32x4 q = src[(int64_t)(dy0 + r) * rs + c];
+        buf[r][4 * c] = q.x;
+        buf[r][4 * c + 1] = q.y;
+        buf[r][4 * c + 2] = q.z;
+        buf[r][4 * c + 3] = q.w;
+      }
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+#pragma unroll
+      for (int dx = 0; dx < F; ++dx) {
+        const float x = buf[r][3 * dx], y = buf[r][3 * dx + 1], z = buf[r][3 * dx + 2];
+        if (finite_f(x) && finite_f(y) && finite_f(z)) {
+          n_fg += 1;
+          sx += (double)x;
+          sy += (double)y;
+          sz += (double)z;
+        }
+      }
+  }
+  float* o = lo + gid * 3;
+  if (2 * n_fg < F * F) {
+    const float qnan = __uint_as_float(0x7fc00000u);
+    o[0] = qnan;
+    o[1] = qnan;
+    o[2] = qnan;
+  } else {
+    const double n = (double)n_fg;
+    o[0] = (float)(sx / n);
+    o[1] = (float)(sy / n);
+    o[2] = (float)(sz / n);
+  }
+}
+
+// Input bytes up to which f = 4 and 8 take the vector variant, whose chain per
+// block is shorter; above, the staged one's whole-line loads count.  Vector /
+// staged in us, the same input again and again (a fresh one each time): f = 8,
+// 4 maps to 32 x 32 5.5 / 6.8 (6.1 / 7.4), 6 to 64 x 64 (18.9 MB) 5.9 / 7.3 (8.0 /
+// 7.9), 10 to 96 x 96 (70.8 MB) 13.3 / 13.3 (17.1 / 15.8); f = 4, 4 to 32 x 32 2.9 /
+// 3.4 (2.9 / 3.4), 24 to 96 x 96 (42.5 MB) 8.0 / 8.4 (10.2 / 10.8), 48 to 128 x 128
+// (151 MB) 24.2 / 25.7 (28.8 / 27.5), 96 to 128 x 128 51.5 / 51.1 (56.2 / 52.0).
+constexpr int64_t kVecMaxBytes = 48ll << 20;
+
 // Order-preserving float <-> uint32 encoding for integer atomics.
 __device__ __forceinline__ uint32_t enc_ord(float f) {
   const uint32_t u = __float_as_uint(f);
@@ -332,7 +404,12 @@ extern "C" int gc_posmap_downsample(const float* pos_hi, int64_t n_maps, int Hr,
   case F_:                                                                                                \
     hipLaunchKernelGGL(k_downsample_staged<F_>, grid, block, 0, stream, pos_hi, n_pix, Hr, Wr, H, W, pos_lat); \
     break
-  switch (f) {
+  const bool vec = (int64_t)nin <= kVecMaxBytes;
+  if (vec && f == 4)
+    hipLaunchKernelGGL(k_downsample_vec<4>, grid, block, 0, stream, pos_hi, n_pix, Hr, Wr, H, W, pos_lat);
+  else if (vec && f == 8)
+    hipLaunchKernelGGL(k_downsample_vec<8>, grid, block, 0, stream, pos_hi, n_pix, Hr, Wr, H, W, pos_lat);
+  else switch (f) {
     GC_STAGED(2);
     GC_STAGED(3);
     GC_STAGED(4);

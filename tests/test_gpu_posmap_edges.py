@@ -1,9 +1,10 @@
-"""The area downsample (every staged factor, a factor without one) and the
-bounding box, bit-exact against the oracle, at the sizes where their launches
-change: pixel counts around a wave's 64 and a block's 256, rows shorter than a
-wave and rows that a wave crosses, several small maps in one wave; assets up to
-and above the one-block bound of the box, sample counts that leave threads
-without a sample, an asset without foreground, infinite positions."""
+"""The area downsample (every staged factor, a factor without one; the factors
+with a variant for small inputs also around its bound) and the bounding box,
+bit-exact against the oracle, at the sizes where their launches change: pixel
+counts around a wave's 64 and a block's 256, rows shorter than a wave and rows
+that a wave crosses, several small maps in one wave; assets up to and above the
+one-block bound of the box, sample counts that leave threads without a sample,
+an asset without foreground, infinite positions."""
 import numpy as np
 import pytest
 import torch
@@ -35,6 +36,20 @@ def test_downsample_matches_oracle(gc, f, n, H, W):
     hi = render(rs, (1, n, H * f, W * f))
     got = gc.gc_posmap_downsample(torch.from_numpy(hi).to(DEV), f).cpu().numpy()
     want = oracle.downsample(hi, f)
+    np.testing.assert_array_equal(got.view(np.int32), want.view(np.int32))
+
+
+@pytest.mark.parametrize("f", [4, 8])
+@pytest.mark.parametrize("H,W", [(1, 63), (5, 13), (3, 65), (8, 8), (1, 257), (33, 31)])
+@pytest.mark.parametrize("more", [0, 1])
+def test_downsample_around_the_small_bound(gc, f, H, W, more):
+    """The last input within the 48 MiB of the variant for small ones, and one map more."""
+    n = (48 << 20) // (H * W * f * f * 12) + more
+    rs = np.random.default_rng(f * 1000 + H * 10 + W)
+    one = render(rs, (1, 53, H * f, W * f))
+    hi = np.tile(one, (1, n // 53 + 1, 1, 1, 1))[:, :n]
+    got = gc.gc_posmap_downsample(torch.from_numpy(hi).to(DEV), f).cpu().numpy()
+    want = np.tile(oracle.downsample(one, f), (1, n // 53 + 1, 1, 1, 1))[:, :n]
     np.testing.assert_array_equal(got.view(np.int32), want.view(np.int32))
 
 
