@@ -37,6 +37,7 @@ constexpr uint8_t kBackground = 255;
 typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(1)));
 typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(1)));
 typedef uint32_t u32_u __attribute__((aligned(1)));
+typedef uint16_t u16_u __attribute__((aligned(1)));
 
 // Wave-wide sum and maximum, returned wave-uniform; every lane of the wave
 // must be active.  Within each row of 16 lanes, DPP moves pair lane i with i
@@ -252,25 +253,112 @@ __device__ __forceinline__ uint32_t valid_bits(int HW, int wi) {
   return n >= 32 ? ~0u : (n <= 0 ? 0u : (1u << n) - 1u);
 }
 
-// Staleness bytes of tokens t0 .. t0 + 4 n - 1 of a row, four per register
-// (token t0 + 4k + j in byte j of d[k]); tokens past the row read as
-// background.  n = 8 (a pair word's tokens) or 2.
-template <int n>
-__device__ __forceinline__ void load_bytes(const uint8_t* __restrict__ row, int HW, int t0, uint32_t (&d)[n]) {
-  if (t0 + 4 * n <= HW) {
-    if constexpr (n == 8) {
-      const u32x4_u lo = *reinterpret_cast<const u32x4_u*>(row + t0);
-      const u32x4_u hi = *reinterpret_cast<const u32x4_u*>(row + t0 + 16);
-      d[0] = lo.x; d[1] = lo.y; d[2] = lo.z; d[3] = lo.w;
-      d[4] = hi.x; d[5] = hi.y; d[6] = hi.z; d[7] = hi.w;
-    } else {
-      const u32x2_u q = *reinterpret_cast<const u32x2_u*>(row + t0);
-      d[0] = q.x;
-      d[1] = q.y;
+// Staleness bytes of tokens t0 .. t0 + 31 of a row, four per register (token
+// t0 + 4k + j in byte j of d[k]); tokens past the row read as background.
+// The row's end is read in one form that depends on HW alone, whose loads are
+// all issued before any is looked at.  (A branch per four tokens there, each
+// with loads of its own to wait for, took the step alone on 6 views of 60 x 60
+// from 3.9 to 5.0 us.)
+__device__ __forceinline__ void load_bytes(const uint8_t* __restrict__ row, int HW, int t0, uint32_t (&d)[8]) {
+  if (t0 + 32 <= HW) {
+    const u32x4_u lo = *reinterpret_cast<const u32x4_u*>(row + t0);
+    const u32x4_u hi = *reinterpret_cast<const u32x4_u*>(row + t0 + 16);
+    d[0] = lo.x; d[1] = lo.y; d[2] = lo.z; d[3] = lo.w;
+    d[4] = hi.x; d[5] = hi.y; d[6] = hi.z; d[7] = hi.w;
+  } else if (HW % 16 == 0) {   // the last word is half full (or past the row)
+    const u32x4_u lo = *reinterpret_cast<const u32x4_u*>(row + min(t0, HW - 16));
+    const uint32_t none = t0 < HW ? 0u : ~0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      d[k] = lo[k] | none;
+      d[4 + k] = ~0u;
     }
+  } else if (HW >= 32) {
+    // the last 32 bytes of the row, of which those in front of t0 (other
+    // tokens', perhaps being stepped meanwhile) are shifted out
+    const u32x4_u lo = *reinterpret_cast<const u32x4_u*>(row + HW - 32);
+    const u32x4_u hi = *reinterpret_cast<const u32x4_u*>(row + HW - 16);
+    d[0] = lo.x; d[1] = lo.y; d[2] = lo.z; d[3] = lo.w;
+    d[4] = hi.x; d[5] = hi.y; d[6] = hi.z; d[7] = hi.w;
+    const int skip = t0 - (HW - 32);   // bytes; 32 and more: nothing of the row is left
+    const int words = skip >> 2;
+#pragma unroll
+    for (int by = 4; by >= 1; by /= 2)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t next = k + by < 8 ? d[k + by < 8 ? k + by : 0] : ~0u;
+        d[k] = words & by ? next : d[k];
+      }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const uint32_t x = __builtin_amdgcn_alignbyte(k < 7 ? d[k < 7 ? k + 1 : 0] : ~0u, d[k], skip & 3);
+      d[k] = words >= 8 ? ~0u : x;
+    }
+  } else {   // rows shorter than that: dwords, or the up to three bytes there are
+    const int last = max(HW - 4, 0);
+    uint32_t x[8];
+    if (HW >= 4) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = *reinterpret_cast<const u32_u*>(row + min(t0 + 4 * k, last));
+    } else {
+      const uint32_t b0 = row[0], b1 = row[min(1, HW - 1)], b2 = row[min(2, HW - 1)];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = (b0 | b1 << 8 | b2 << 16) | ~0u << (8 * HW);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int skip = t0 + 4 * k - min(t0 + 4 * k, last);
+      const uint32_t y = __builtin_amdgcn_alignbyte(~0u, x[k], skip & 3);
+      d[k] = skip >= 4 ? ~0u : y;
+    }
+  }
+}
+
+// The reverse; at the end of a row that the accesses straddle, the r tokens
+// left go out in the powers of two that make up r, largest first.
+__device__ __forceinline__ void store_bytes(uint8_t* __restrict__ row, int HW, int t0, const uint32_t (&d)[8]) {
+  uint8_t* to = row + t0;
+  const int r = HW - t0;
+  if (r >= 32) {
+    *reinterpret_cast<u32x4_u*>(to) = u32x4_u{d[0], d[1], d[2], d[3]};
+    *reinterpret_cast<u32x4_u*>(to + 16) = u32x4_u{d[4], d[5], d[6], d[7]};
+  } else if (r > 0) {
+    if (r & 16) *reinterpret_cast<u32x4_u*>(to) = u32x4_u{d[0], d[1], d[2], d[3]};
+    to += r & 16;
+    // what is left, from its first token on (picked by masks: a choice between
+    // elements would make the compiler index d, and move it to memory)
+    const uint32_t m = r & 16 ? ~0u : 0u;
+    uint32_t e0 = (d[4] & m) | (d[0] & ~m), e1 = (d[5] & m) | (d[1] & ~m);
+    const uint32_t e2 = (d[6] & m) | (d[2] & ~m), e3 = (d[7] & m) | (d[3] & ~m);
+    if (r & 8) {
+      *reinterpret_cast<u32x2_u*>(to) = u32x2_u{e0, e1};
+      e0 = e2;
+      e1 = e3;
+      to += 8;
+    }
+    if (r & 4) {
+      *reinterpret_cast<u32_u*>(to) = e0;
+      e0 = e1;
+      to += 4;
+    }
+    if (r & 2) {
+      *reinterpret_cast<u16_u*>(to) = (uint16_t)e0;
+      e0 >>= 16;
+      to += 2;
+    }
+    if (r & 1) *to = (uint8_t)e0;
+  }
+}
+
+// The same for tokens t0 .. t0 + 7.
+__device__ __forceinline__ void load_bytes(const uint8_t* __restrict__ row, int HW, int t0, uint32_t (&d)[2]) {
+  if (t0 + 8 <= HW) {
+    const u32x2_u q = *reinterpret_cast<const u32x2_u*>(row + t0);
+    d[0] = q.x;
+    d[1] = q.y;
   } else {   // the row's end
 #pragma unroll
-    for (int k = 0; k < n; ++k) {
+    for (int k = 0; k < 2; ++k) {
       const int t = t0 + 4 * k;
       if (t + 4 <= HW) {
         d[k] = *reinterpret_cast<const u32_u*>(row + t);
@@ -284,18 +372,12 @@ __device__ __forceinline__ void load_bytes(const uint8_t* __restrict__ row, int 
   }
 }
 
-template <int n>
-__device__ __forceinline__ void store_bytes(uint8_t* __restrict__ row, int HW, int t0, const uint32_t (&d)[n]) {
-  if (t0 + 4 * n <= HW) {
-    if constexpr (n == 8) {
-      *reinterpret_cast<u32x4_u*>(row + t0) = u32x4_u{d[0], d[1], d[2], d[3]};
-      *reinterpret_cast<u32x4_u*>(row + t0 + 16) = u32x4_u{d[4], d[5], d[6], d[7]};
-    } else {
-      *reinterpret_cast<u32x2_u*>(row + t0) = u32x2_u{d[0], d[1]};
-    }
+__device__ __forceinline__ void store_bytes(uint8_t* __restrict__ row, int HW, int t0, const uint32_t (&d)[2]) {
+  if (t0 + 8 <= HW) {
+    *reinterpret_cast<u32x2_u*>(row + t0) = u32x2_u{d[0], d[1]};
   } else {
 #pragma unroll
-    for (int k = 0; k < n; ++k) {
+    for (int k = 0; k < 2; ++k) {
       const int t = t0 + 4 * k;
       if (t + 4 <= HW) {
         *reinterpret_cast<u32_u*>(row + t) = d[k];
@@ -392,10 +474,10 @@ __global__ __launch_bounds__(kRowBlock) void k_cov_update(const uint32_t* __rest
   for (int wi = (int)threadIdx.x; wi < wpr; wi += kRowBlock) {
     const uint32_t fresh = set_covers(bits, B, N, wpr, anchor_mask, b, v, wi) & valid_bits(HW, wi);
     uint32_t d[8];
-    load_bytes<8>(row, HW, wi * 32, d);
+    load_bytes(row, HW, wi * 32, d);
     step_word(d, fresh);
     st.add(d, R);
-    store_bytes<8>(row, HW, wi * 32, d);
+    store_bytes(row, HW, wi * 32, d);
   }
   st.write(stats + (int64_t)bv * 4);
 }
@@ -534,7 +616,7 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
     const int wi = active ? (int)(wg - (int64_t)bv * wpr) : 0;
     const int b = bv / N, v = bv - b * N;
     uint32_t d[2] = {~0u, ~0u};   // staleness bytes of the lane's 8 tokens (background past the row)
-    if (active) load_bytes<2>(stale + (int64_t)bv * HW, HW, wi * 32 + 8 * sub, d);
+    if (active) load_bytes(stale + (int64_t)bv * HW, HW, wi * 32 + 8 * sub, d);
     uint32_t pb[kHistViews];      // the other views' pair bits of these 8 tokens
 #pragma unroll
     for (int u = 0; u < kHistViews; ++u)
@@ -561,7 +643,7 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
           c_max = max(c_max, x);
         }
       }
-      if (active) store_bytes<2>(stale + (int64_t)bv * HW, HW, wi * 32 + 8 * sub, d);
+      if (active) store_bytes(stale + (int64_t)bv * HW, HW, wi * 32 + 8 * sub, d);
       // per-row statistics: one atomic per counter for a wave within one row
       const int bv0 = __builtin_amdgcn_readfirstlane(bv);   // lane 0 is always active
       if (__ballot(active && bv != bv0) == 0ull) {
@@ -769,7 +851,7 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_round(const uint32_t* __restr
     bv = (int)(it / cpr);
     wi = (int)(it - (int64_t)bv * cpr) * 64 + lane;
     const int b = bv / N, v = bv - b * N;
-    load_bytes<8>(stale + (int64_t)bv * HW, HW, wi * 32, d);
+    load_bytes(stale + (int64_t)bv * HW, HW, wi * 32, d);
 #pragma unroll
     for (int q = 0; q < VPW; ++q) {
       const int u = q * kSelWaves + wv;
@@ -794,7 +876,7 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_round(const uint32_t* __restr
     const uint32_t live = wi < wpr ? valid_bits(HW, wi) & ~covered(chosen) : 0u;
     if constexpr (UPDATE) {   // after the barrier: every wave has read the old bytes
       step_word(d, wi < wpr ? covered(anchor_mask) & valid_bits(HW, wi) : 0u);
-      if (wv == 0) store_bytes<8>(stale + (int64_t)bv * HW, HW, wi * 32, d);
+      if (wv == 0) store_bytes(stale + (int64_t)bv * HW, HW, wi * 32, d);
     }
     if (__ballot(live != 0u)) {
 #pragma unroll
@@ -846,7 +928,7 @@ __global__ __launch_bounds__(kSelBlock) void k_score_pass(const uint32_t* __rest
     const bool in = wi < wpr;
     uint8_t* row = stale + (int64_t)bv * HW;
     uint32_t d[8];
-    load_bytes<8>(row, HW, wi * 32, d);
+    load_bytes(row, HW, wi * 32, d);
     for (int u = wv; u < N; u += kSelWaves)
       word[u][lane] = !in ? 0u : u == v ? ~0u : pair_word(bits, B, N, wpr, u, b, v, wi);
     __syncthreads();
@@ -855,7 +937,7 @@ __global__ __launch_bounds__(kSelBlock) void k_score_pass(const uint32_t* __rest
       uint32_t fresh = 0u;
       for (unsigned long long m = anchor_mask; m; m &= m - 1) fresh |= word[__ffsll((long long)m) - 1][lane];
       step_word(d, fresh & live);
-      if (wv == 0) store_bytes<8>(row, HW, wi * 32, d);   // after the barrier: every wave has read the old bytes
+      if (wv == 0) store_bytes(row, HW, wi * 32, d);   // after the barrier: every wave has read the old bytes
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) d[k] = bytes_plus_one(d[k]);
@@ -900,7 +982,7 @@ __global__ __launch_bounds__(kRowBlock) void k_cov_final(const SelState* st, int
     RowStats rs;
     for (int wi = (int)threadIdx.x; wi < wpr; wi += kRowBlock) {
       uint32_t d[8];
-      load_bytes<8>(row, HW, wi * 32, d);
+      load_bytes(row, HW, wi * 32, d);
       rs.add(d, R);
     }
     rs.write(stats + (int64_t)blockIdx.x * 4);
