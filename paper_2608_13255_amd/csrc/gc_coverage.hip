@@ -763,6 +763,7 @@ constexpr int kSelBlock = 256;
 constexpr int kSelWaves = kSelBlock / 64;
 constexpr int kRedBlocks = 1024;   // partial sums per candidate that the workspace holds
 constexpr int kSelBlocks = 512;    // 8 x 16 views of 128 x 128 (1024 items): 256 / 512 blocks 40 / 38 us
+static_assert(kSelWaves == 4, "k_score_pass deals every fourth view");
 static_assert(kSelBlocks <= kRedBlocks, "the workspace holds the partial sums");
 constexpr int kFlushItems = 4096;  // items whose sums fit a lane's and a wave's 32 bits (32 * 255 * 64 * 4096 < 2^32)
 
@@ -771,15 +772,28 @@ struct SelState {
   unsigned long long chosen[GC_MAX_ANCHORS + 1];          // views chosen before round r
 };
 
+// Blocks of a score pass: more of them where their partials stay few enough
+// for the one block that adds them up (8 assets x 16 views of 128 x 128, one set:
+// 512 / 2048 blocks 7.5 / 6.6 us).
+constexpr int kScoreBlocks = 2048;
+static_assert(kScoreBlocks <= 2 * kRedBlocks, "a score pass uses both rounds' partials");
+int score_blocks(int64_t n_items, int M) {
+  int64_t n = (int64_t)kSelBlocks * GC_MAX_VIEWS / M;
+  if (n > kScoreBlocks) n = kScoreBlocks;
+  return (int)(n_items < n ? n_items : n);
+}
+
 int sel_blocks(int64_t n_items) { return (int)(n_items < kSelBlocks ? n_items : kSelBlocks); }
 
 // The sums over the blocks' partials of candidates 0 .. n - 1 to out (LDS);
 // every thread of the block (a multiple of 64, at least GC_MAX_VIEWS) calls it,
 // and it ends on a barrier.  A thread's stride is a multiple of n, so it adds
-// one candidate's partials from coalesced loads that depend on nothing.
+// one candidate's partials from coalesced loads that depend on nothing.  At most
+// kSumThreads threads per candidate: their additions to out go to one address.
+constexpr int kSumThreads = 128;
 __device__ __forceinline__ void sum_partials(const unsigned long long* __restrict__ part, int n, int nblk,
                                              unsigned long long* out) {
-  const int t = (int)threadIdx.x, T = (int)blockDim.x / n * n;
+  const int t = (int)threadIdx.x, T = min((int)blockDim.x / n, kSumThreads) * n;
   if (t < n) out[t] = 0ull;
   unsigned long long acc = 0ull;
   if (t < T) {
@@ -909,12 +923,16 @@ __global__ __launch_bounds__(kSelBlock) void k_sel_round(const uint32_t* __restr
 }
 
 // Partial scores of the M sets: 1 + staleness over the foreground tokens a set
-// covers.  The item's pair words are put in LDS once, for every set.
+// covers.  The item's pair words are put in LDS once, for every set: those of
+// the views in need, which some set (or the step's anchor set) holds.
+// 15 assets x 64 views of 64 x 64, one set of three views: 10.3 us; 26.7 with
+// every view's words, one load after another.
 template <bool UPDATE>
 __global__ __launch_bounds__(kSelBlock) void k_score_pass(const uint32_t* __restrict__ bits,
                                                           uint8_t* __restrict__ stale, int B, int N, int HW, int wpr,
-                                                          SelState* st, SetMasks sets, int M,
+                                                          SelState* st, SetMasks sets, int M, unsigned long long need,
                                                           unsigned long long anchor_mask) {
+  constexpr int kLoads = 4;
   __shared__ uint32_t word[GC_MAX_VIEWS][64];
   const int lane = __lane_id();
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
@@ -929,8 +947,20 @@ __global__ __launch_bounds__(kSelBlock) void k_score_pass(const uint32_t* __rest
     uint8_t* row = stale + (int64_t)bv * HW;
     uint32_t d[8];
     load_bytes(row, HW, wi * 32, d);
-    for (int u = wv; u < N; u += kSelWaves)
-      word[u][lane] = !in ? 0u : u == v ? ~0u : pair_word(bits, B, N, wpr, u, b, v, wi);
+    // every fourth view for each wave; a view past the last repeats it
+    for (unsigned long long m = need & (0x1111111111111111ull << wv); m;) {   // uniform
+      int u[kLoads];
+      uint32_t x[kLoads];
+#pragma unroll
+      for (int q = 0; q < kLoads; ++q) {
+        u[q] = m ? __ffsll((long long)m) - 1 : u[q > 0 ? q - 1 : 0];
+        m &= m - 1;
+        x[q] = pair_word(bits, B, N, wpr, u[q], b, v, min(wi, wpr - 1));
+      }
+#pragma unroll
+      for (int q = 0; q < kLoads; ++q) word[u[q]][lane] = !in ? 0u : u[q] == v ? ~0u : x[q];
+    }
+    if constexpr (UPDATE) __builtin_amdgcn_s_waitcnt(kWaitVm0);   // the old bytes, which wave 0 overwrites
     __syncthreads();
     const uint32_t live = in ? valid_bits(HW, wi) : 0u;
     if constexpr (UPDATE) {
@@ -1225,15 +1255,17 @@ void launch_score(const uint32_t* pair_bits, uint8_t* stale, int B, int N, size_
   }
   SelState* st = static_cast<SelState*>(workspace);
   const int wpr = (int)((HW + 31) / 32);
-  const int nblk = sel_blocks((int64_t)B * N * ((wpr + 63) / 64));
+  const int nblk = score_blocks((int64_t)B * N * ((wpr + 63) / 64), M);
+  unsigned long long need = upd ? mask_upd : 0ull;
+  for (int m = 0; m < M; ++m) need |= masks.m[m];
   if (upd) {
     hipLaunchKernelGGL(k_score_pass<true>, dim3((unsigned)nblk), dim3(kSelBlock), 0, stream, pair_bits, stale, B, N,
-                       (int)HW, wpr, st, masks, M, mask_upd);
+                       (int)HW, wpr, st, masks, M, need, mask_upd);
     hipLaunchKernelGGL((k_cov_final<true, true>), dim3((unsigned)(B * N)), dim3(kRowBlock), 0, stream, st, N, 0, nblk,
                        0ull, nullptr, M, out, stale, (int)HW, wpr, R, stats);
   } else {
     hipLaunchKernelGGL(k_score_pass<false>, dim3((unsigned)nblk), dim3(kSelBlock), 0, stream, pair_bits, stale, B, N,
-                       (int)HW, wpr, st, masks, M, 0ull);
+                       (int)HW, wpr, st, masks, M, need, 0ull);
     hipLaunchKernelGGL((k_cov_final<true, false>), dim3(1), dim3(kRowBlock), 0, stream, st, N, 0, nblk, 0ull, nullptr,
                        M, out, nullptr, 0, 0, 1, nullptr);
   }

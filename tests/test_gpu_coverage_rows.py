@@ -2,7 +2,9 @@
 and the scores (both kernel families: up to twelve views, and more): rows
 shorter than a lane's 8 or 32 tokens, rows that end at or around a dword, a
 lane's tokens, a pair word or an item of 64 words, at several byte offsets;
-bit-exact against the oracle, and nothing written around the rows."""
+bit-exact against the oracle, and nothing written around the rows.  Scores of
+few and many sets with more than twelve views: the sets' views and the step's
+anchors apart, items below and above the pass's blocks."""
 import numpy as np
 import pytest
 import torch
@@ -48,3 +50,25 @@ def test_row_ends(gc, N, n):
         np.testing.assert_array_equal(st_d.cpu().numpy(), st_o)
     buf[offset:offset + stale.size] = 0
     assert not buf.any()
+
+
+@pytest.mark.parametrize("N,B,H,W", [(13, 2, 9, 9), (64, 9, 30, 41), (13, 85, 3, 683)])
+def test_scores_of_few_sets(gc, N, B, H, W):
+    rs, seen, words, stale = random_case(4000 + N, B, N, H, W, density=0.2)
+    bits = torch.from_numpy(words.view(np.int32)).to(DEV)
+    st_d, _ = device_stale(stale, 3)
+    ws = torch.empty(gc.gc_coverage_workspace_bytes(), dtype=torch.uint8, device=DEV)
+    st_o = stale
+    for M, a in ((1, 1), (2, 2), (3, 1), (9, 3), (64, 4)):
+        ws.fill_(255)
+        sets = [sorted(rs.choice(N - 2, a, replace=False).tolist()) for _ in range(M)]
+        A = [N - 1] if M % 2 else [N - 2, 0]
+        stats, sc = gc.gc_coverage_update_score(bits, st_d, A, 2, sets, workspace=ws)
+        st_o, stats_o = oracle.coverage_update(st_o, seen, A, 2)
+        want = oracle.coverage_score(st_o, seen, sets)
+        np.testing.assert_array_equal(st_d.cpu().numpy(), st_o)
+        np.testing.assert_array_equal(stats.cpu().numpy().view(np.uint32), stats_o)
+        np.testing.assert_array_equal(sc.cpu().numpy().view(np.uint64), want)
+        ws.fill_(255)
+        sc = gc.gc_coverage_score(bits, st_d, sets, workspace=ws)
+        np.testing.assert_array_equal(sc.cpu().numpy().view(np.uint64), want)
