@@ -11,7 +11,8 @@
 // Small chunks: with larger ones fewer groups of 64 are partly filled, but a
 // dense block's chain of groups grows while its neighbours are empty (8 assets
 // x 12 views of 128 x 128: visibility pairs with chunks of 256 / 512 / 1024
-// tokens 28 / 30 / 37 us, builder with 128 / 256 17.9 / 19.6 us).
+// tokens 28 / 30 / 37 us, builder with 128 / 256 17.9 / 19.6 us).  For the same
+// reason launches of few chunks do without: both kernels have a direct form.
 #pragma once
 
 #include "gc_common.h"

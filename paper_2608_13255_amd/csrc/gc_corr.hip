@@ -148,7 +148,7 @@ __device__ __forceinline__ void build_pair(const BuildArgs& g, const float (&P)[
 // COMPACT: a block compacts the foreground tokens of a chunk of one target
 // view, writes the other tokens' zero words, and then gives each (compacted
 // token, anchor slot) a lane: a group of G = 4 or 8 adjacent lanes serves one
-// token (lanes with slot >= a idle).  Bound by vector-ALU issue (12 of 17.9 us)
+// token (lanes with slot >= a idle).  Bound by vector-ALU issue (10 of 17.9 us)
 // and by the chain of a block's loads: 8 assets x 8 target views of 128 x 128
 // with 4 anchors 17.9 us, 21.5 with the counters, against 20.5 and 30.6
 // without the compaction.

@@ -69,7 +69,9 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 
 constexpr int kCompactTok = 256;   // tokens per chunk, and threads per block
 constexpr int kCompactWaves = kCompactTok / 64;
-constexpr int kPairBatch = 2;   // anchors whose tap loads a wave keeps in flight together (before the rotation 1: 45 us, 2 and 3: 35, 4: 39)
+// anchors whose tap loads a wave keeps in flight together (before the rotation
+// 1: 45 us, 2 and 3: 35, 4: 39)
+constexpr int kPairBatch = 2;
 
 // Ballots m[q] of the lanes whose token P (live: one to look at) anchor u0 + q
 // of asset b sees; u0 is wave-uniform, and an anchor past the last view repeats
@@ -101,7 +103,7 @@ __device__ __forceinline__ void pair_ballots(const float (&P)[3], bool live, con
 // turn, each leaving one ballot per anchor, and the rows' bits are put
 // together from the ballots by the tokens' ranks.  The anchor is the same for
 // a whole wave, so its camera sits in scalar registers.
-// Bound by vector-ALU issue (23 of 28 us; two IEEE divisions and four tap
+// Bound by vector-ALU issue (21 of 28 us; two IEEE divisions and four tap
 // distances per pair).  8 assets x 12 views of 128 x 128: 78 -> 28 us against a
 // lane per raster token and anchor, which also formed the unused weights.
 __global__ __launch_bounds__(kCompactTok) void k_cov_pairs(const float* __restrict__ pos,
@@ -227,10 +229,9 @@ __global__ __launch_bounds__(kBlock) void k_cov_init(const float* __restrict__ p
 }
 
 // The token kernels give each lane one pair word: 32 consecutive tokens of
-// a row, the staleness bytes of those tokens (two 16-byte loads, or bytewise
-// when the rows are not 16-byte aligned) and, per view, one coalesced uint32
-// of the pair bits.  A 64-lane wave covers 2048 tokens of one (asset, view)
-// row: an item.  Per-item sums go through one wave sum each.
+// a row, the staleness bytes of those tokens (two 16-byte loads at any
+// address) and, per view, one coalesced uint32 of the pair bits.  The 64 lanes
+// of a wave cover 2048 tokens of one (asset, view) row: an item.
 
 __device__ __forceinline__ uint32_t pair_word(const uint32_t* __restrict__ bits, int B, int N, int wpr, int u, int b,
                                               int v, int wi) {
@@ -749,11 +750,10 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
 // workspace and every block of the next launch adds them up and picks the
 // round's view itself: no launch in between, no atomics, nothing to clear.
 //
-// Bound by launches and latency: a round takes about 6 us at 2 assets x 20
-// views of 95 x 97, of which the pass itself is about two.  Update + selection
-// of 5 views there: 96 -> 38 us against update, and per round a pass of
-// one-wave blocks and a pick; set scores 33 -> 16 us; 64 views of 96 x 96 with
-// 8 anchors 232 -> 104 us.
+// Bound by launches and latency.  Update + selection of 5 views at 2 assets x 20
+// views of 95 x 97: 96 -> 33 us against an update and, per round, a pass of
+// one-wave blocks and a pick; update + the scores of 20 sets 33 -> 10.4 us; 64
+// views of 96 x 96 with 8 anchors 232 -> 105 us.
 //
 // A block's four waves share an item (64 pair words of one row, a word per
 // lane); each takes every fourth view.  The weights are turned into bit
@@ -761,7 +761,10 @@ __global__ __launch_bounds__(kHistThreads) void k_cov_hist(const uint32_t* __res
 // per plane that occurs (staleness is small: two or three of eight).
 constexpr int kSelBlock = 256;
 constexpr int kSelWaves = kSelBlock / 64;
-constexpr int kRedBlocks = 1024;   // partial sums per candidate that the workspace holds
+// Partial sums per candidate and round that the workspace holds: twice what a
+// round's launch uses, so that its size stays the one callers have been told
+// (gc_coverage_workspace_bytes) whatever their views.
+constexpr int kRedBlocks = 1024;
 constexpr int kSelBlocks = 512;    // 8 x 16 views of 128 x 128 (1024 items): 256 / 512 blocks 40 / 38 us
 static_assert(kSelWaves == 4, "k_score_pass deals every fourth view");
 static_assert(kSelBlocks <= kRedBlocks, "the workspace holds the partial sums");

@@ -143,6 +143,11 @@ __device__ __forceinline__ void finish_item(const GArgs& g, int64_t e, const typ
     if (g.u.need_m2) CD::unpack(sd.m2, m2);
     if (g.u.need_m1) CD::unpack(sd.m1, m1);
     unipc_vec<VEC>(g.u, xin, m2, m1, mk, xc, xn);
+    // nontemporal: a cached x_c, as the stored-operator step has, is ahead in a
+    // trajectory and behind other work and behind on fresh buffers here too (8 x
+    // 12 views of 128 x 128 x 16 bf16, 2 anchors: 62.2 -> 58.5, 70.4 -> 68.0, 61.5
+    // -> 65.0 us), and no better on few channels (4 x 6 of 96 x 96 x 16 f32, 4
+    // anchors, in a trajectory 19.5 -> 20.4)
     CD::store_stream(g.x_c, e, CD::pack(xc));
     CD::store_stream(g.x_next, e, CD::pack(xn));
   }

@@ -23,13 +23,14 @@
 // Two passes, deterministic:
 //   bits     streams the input once in token order: one 64-bit ballot per wave
 //            gives the bitmask, and each chunk of 1024 tokens its count
-//   scatter  a block per 1024 consecutive list positions, from the bitmask
-//            alone (32 or 96 times smaller than the input): token order and
-//            list order agree at the start of every band, so the number of
-//            listed tokens in front of the block is the sum of the counts up
-//            to its band, plus the bits of its band's columns and tile rows in
-//            front of it; inside the block tokens are ranked by (round, wave,
-//            mbcnt of the ballot)
+//   scatter  a block per 1024 consecutive list positions, placed by the
+//            bitmask alone (32 a or 96 times smaller than the words of a
+//            anchors or the positions; only a record's position is read
+//            again): token order and list order agree at the start of every
+//            band, so the number of listed tokens in front of the block is the
+//            sum of the counts up to its band, plus the bits of its band's
+//            columns and tile rows in front of it; inside the block tokens are
+//            ranked by (round, wave, mbcnt of the ballot)
 // Above kPrefixChunks chunks a one-block pass between the two turns the counts
 // into offsets.
 // Bound by launches and latency up to the stress size: 8 assets x 8 target

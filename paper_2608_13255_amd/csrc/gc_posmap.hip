@@ -51,8 +51,13 @@ __global__ __launch_bounds__(kBlock) void k_downsample(const float* __restrict__
   }
 }
 
-// Staged variant for the factors in use: a wave takes 64 consecutive latent
-// pixels.  Per render row their segments (3F floats each) are read as aligned
+// Staged variant: a wave takes 64 consecutive latent pixels.  Its vectors and
+// rows in flight are unrolled for the factor, so it exists for the factors that
+// renders and latent grids of this library's workloads have between them (2, 3,
+// 4, 6, 8, 16); every other one takes the direct kernel, at the cost of its
+// strided loads: 10 maps to 96 x 96 by 5 10.4 us and by 10 53.8, 6 to 64 x 64 by
+// 12 50.1 (by 16, staged, 19.7), 6 to 32 x 32 by 32 333.
+// Per render row the pixels' segments (3F floats each) are read as aligned
 // vectors in memory order, one per lane, so that every load instruction covers
 // whole lines, and are handed to the pixels' lanes through the wave's own LDS
 // (no barrier: LDS operations of one wave keep their order); the next rows'
@@ -356,7 +361,7 @@ __global__ __launch_bounds__(kBoxBlock) void k_bbox_accum(const float* __restric
     }
   }
   uint32_t* a = acc + (int64_t)b * 8;
-  if (gridDim.x > 1) {
+  if (gridDim.x > 1) {   // the ticket's release waits for its own wave, which is the one that adds
     if (threadIdx.x < 3) atomicMin(a + threadIdx.x, fold);
     else if (threadIdx.x < 6) atomicMax(a + threadIdx.x, fold);
     else if (threadIdx.x == 6) atomicOr(a + 7, fold);

@@ -175,8 +175,11 @@ __device__ __forceinline__ void token_step(const TArgs& g, int b, int p, int cv,
     if (g.u.need_m2) CD::unpack(m2r, m2);
     if (g.u.need_m1) CD::unpack(m1r, m1);
     unipc_vec<VEC>(g.u, xin, m2, m1, x0f, xc, xn);
-    // x_c is the next step's x_prev: a cached store (8 x 12 views of 128 x 128
-    // x 16 bf16: 63.0 -> 60.7 us; x_next cached as well 62.0)
+    // x_c is the next step's x_prev: a cached store.  8 x 12 views of 128 x 128 x
+    // 16 bf16 with 2 anchors, nontemporal / cached: steps of one trajectory
+    // 60.3 / 55.4 us, behind other work that streams 1 GB 70.3 / 67.0; calls back
+    // to back on 2 GB of other buffers, where one call's write-backs fall into
+    // the next, 61.5 / 66.3
     CD::store(g.x_c, base, CD::pack(xc));
     CD::store_stream(g.x_next, base, CD::pack(xn));
   }
@@ -279,9 +282,10 @@ __global__ __launch_bounds__(kBlock) void k_reconstruct(const void* __restrict__
 
 // HBM-bound, four streams in and two out.  All loads are issued before any is
 // used, and the outputs, which the next step reads, are plain stores: 8 x 12
-// views of 128 x 128 x 16 bf16 51.5 -> 48.5 us (6.2 TB/s; 49.4 with
-// nontemporal stores; two or four vectors per lane 50.0 / 52.0, 512-lane
-// blocks 48.3).
+// views of 128 x 128 x 16 bf16 51.5 -> 48.5 us (6.2 TB/s; two or four vectors per
+// lane 50.0 / 52.0, 512-lane blocks 48.3).  Nontemporal / plain stores: three
+// states in turn 49.4 / 48.5, steps of one trajectory 47.7 / 47.9, behind other
+// work 53.3 / 52.6, back to back on 2 GB of other buffers 49.6 / 51.6.
 template <int DT, int VEC>
 __global__ __launch_bounds__(kBlock) void k_unipc(TArgs g, const void* __restrict__ m_k, int64_t n_vec) {
   using CD = Codec<DT, VEC>;

@@ -4,9 +4,8 @@ distinguish:
   * rows of a multiple of 32 tokens, 16-byte aligned (two 16-byte accesses
     per lane);
   * rows of 16 mod 32 tokens (the last word of a row half full);
-  * ragged rows (1961 tokens: bytewise accesses, a partial last word);
-  * a staleness tensor that starts one byte past an aligned address
-    (bytewise accesses although the rows are whole words);
+  * ragged rows (1961 tokens: a partial last word, rows at any byte);
+  * a staleness tensor that starts one byte past an aligned address;
   * more 2048-token items than reduction blocks (blocks stride over items);
   * 12 views (the coverage-histogram path at its largest) and 14 views (the
     per-round passes that serve more views), aligned and ragged.
