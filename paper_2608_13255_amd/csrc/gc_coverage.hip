@@ -776,10 +776,9 @@ struct SelState {
 };
 
 // Blocks of a score pass: more of them where their partials stay few enough
-// for the one block that adds them up (8 assets x 16 views of 128 x 128, one set:
-// 512 / 2048 blocks 7.5 / 6.6 us).
+// for the one block that adds them up, no more than of the largest selection (8
+// assets x 16 views of 128 x 128, one set: 512 / 2048 blocks 7.5 / 6.6 us).
 constexpr int kScoreBlocks = 2048;
-static_assert(kScoreBlocks <= 2 * kRedBlocks, "a score pass uses both rounds' partials");
 int score_blocks(int64_t n_items, int M) {
   int64_t n = (int64_t)kSelBlocks * GC_MAX_VIEWS / M;
   if (n > kScoreBlocks) n = kScoreBlocks;
